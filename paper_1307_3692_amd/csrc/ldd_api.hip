@@ -123,7 +123,6 @@ struct Workspace {
   int num_cu = 0;
   int max_coresident = 0;  // co-resident blocks of the persistent round kernel
   int block_coresident = 0;  // co-resident workgroups of the workgroup engine (a team's bound)
-  int lds_bytes = 0;       // dynamic LDS the workgroup engine may take (0: the device refused the size)
 };
 
 std::mutex g_ws_mu;
@@ -157,12 +156,6 @@ ldd_status ws_setup(Workspace& w) {
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_block, reinterpret_cast<const void*>(k_block_decompose),
                                                          1024, 0));
     w.block_coresident = w.num_cu * std::max(per_cu_block, 1);
-    // the workgroup engine's dynamic LDS for small graphs (beside its static LDS)
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_decompose), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            BLOCK_LDS_BYTES) == hipSuccess)
-      w.lds_bytes = BLOCK_LDS_BYTES;
-    else
-      (void)hipGetLastError();
   }
   ldd_status s;
   if ((s = grow(w.ctrl, sizeof(Ctrl))) || (s = grow(w.st, 2 * sizeof(RoundState))) ||
@@ -670,7 +663,7 @@ static ldd_status block_status(unsigned err, u64 delta, int n) {
                   (unsigned long long)delta);
     return LDD_ERR_OVERFLOW;
   }
-  if (err & (BLK_WIDE | BLK_SKEW)) return REDO_MULTI;
+  if (err & (BLK_WIDE | BLK_SKEW | BLK_QUEUE)) return REDO_MULTI;
   if (err) {
     ldd_set_error("workgroup engine error flags 0x%x", err);
     return LDD_ERR_INTERNAL;
@@ -706,24 +699,19 @@ static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t*
   BlockJob j{};
   j.n = n;
   j.nnz = g->nnz;
-  j.row_ptr = g->row_ptr;
-  j.col = g->col_idx;
-  j.shift = (const long long*)shift_fix;
-  j.centre = centre;
-  j.P = (u64*)w.P.p;
-  j.wk = (u64*)w.bk_wq.p;
-  j.wake = (int*)w.bk_wq.p;
-  j.q0 = (int*)w.bk_wq.p + 2 * (long long)n;
-  j.q1 = (int*)w.bk_wq.p + 3 * (long long)n;
+  j.row_ptr = (g_cint*)g->row_ptr;
+  j.col = (g_cint*)g->col_idx;
+  j.shift = (g_ci64*)shift_fix;
+  j.centre = (g_int*)centre;
+  j.P = (g_u64*)w.P.p;
+  j.wk = (g_u64*)w.bk_wq.p;
+  j.wake = (g_int*)w.bk_wq.p;
+  j.q0 = (g_int*)w.bk_wq.p + 2 * (long long)n;
+  j.q1 = (g_int*)w.bk_wq.p + 3 * (long long)n;
   j.tail_den = tail_den_of(opt);
   j.team = K;
-  j.sync = K > 1 ? (TeamSync*)w.bk_sync.p : nullptr;
+  j.sync = K > 1 ? (g_sync*)w.bk_sync.p : nullptr;
   j.deg_cap = deg_cap;
-  // the dynamic LDS the graph's mode needs (the label-correcting iteration, or the rounds in LDS)
-  long long lds = 0;
-  if (K == 1 && fix_lds_bytes(n, g->nnz) <= w.lds_bytes) lds = fix_lds_bytes(n, g->nnz);
-  else if (K == 1 && rounds_lds_bytes(n) <= w.lds_bytes) lds = rounds_lds_bytes(n);
-  const int lds_bytes = (int)((lds + 15) & ~15ll);
   HIP_TRY(hipStreamWaitEvent(st, w.ev[2], 0));  // after any step a previous call left queued
   if (stats) HIP_TRY(hipEventRecord(w.ev[0], st));
   if (K > 1)
@@ -736,8 +724,8 @@ static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t*
   HIP_TRY(hipHostGetDevicePointer(&bout_dev, &w.host->bout, 0));
   volatile BlockOut* vb = &w.host->bout;
   vb->ready = 0;
-  hipLaunchKernelGGL(k_block_decompose, dim3(K), dim3(1024), (size_t)lds_bytes, st, (const BlockJob*)nullptr,
-                     (const TeamJob*)nullptr, K, (unsigned*)nullptr, (BlockOut*)bout_dev, j, lds_bytes);
+  hipLaunchKernelGGL(k_block_decompose, dim3(K), dim3(1024), 0, st, (const BlockJob*)nullptr, (const TeamJob*)nullptr, K,
+                     (unsigned*)nullptr, (BlockOut*)bout_dev, j);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(w.ev[2], st));
   for (unsigned spin = 0; !vb->ready; ++spin) {
@@ -984,12 +972,8 @@ ldd_status ldd_batch_workgroup(int32_t G, const int64_t* vtx_off, const int64_t*
       hipLaunchKernelGGL(k_fill_u64, dim3(grid_for((long long)nteams * sizeof(TeamSync) / 8, 256, 1024)), dim3(256), 0,
                          st, (u64*)w.bk_sync.p, (long long)nteams * (long long)(sizeof(TeamSync) / 8), 0ull);
     if (grid > njobs) grid = njobs;
-    // small graphs keep their state in LDS when the grid is one workgroup per CU (the LDS then costs
-    // no residency: one workgroup of 1024 threads per CU either way)
-    const int lds_bytes = grid <= w.num_cu ? w.lds_bytes : 0;
-    hipLaunchKernelGGL(k_block_decompose, dim3(grid), dim3(1024), (size_t)lds_bytes, st, (const BlockJob*)w.bk_jobs.p,
-                       (const TeamJob*)w.bk_order.p, njobs, (unsigned*)w.bk_cnt.p, (BlockOut*)w.bk_out.p, BlockJob{},
-                       lds_bytes);
+    hipLaunchKernelGGL(k_block_decompose, dim3(grid), dim3(1024), 0, st, (const BlockJob*)w.bk_jobs.p,
+                       (const TeamJob*)w.bk_order.p, njobs, (unsigned*)w.bk_cnt.p, (BlockOut*)w.bk_out.p, BlockJob{});
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(w.ev[2], st));
     std::vector<BlockOut> outs((size_t)G);

@@ -17,18 +17,20 @@
 // (small graphs, high-diameter graphs) run far faster here; a batch runs one graph per workgroup,
 // the largest first, each workgroup taking the next graph when it finishes one.
 //
-// Top-down is arc-balanced inside the workgroup: a chunk of RT frontier entries is staged in LDS
-// (first arc, degree prefix, offer) and every thread takes arcs of the chunk by index, finding its
-// entry by binary search, so a high-degree vertex is shared by all threads.
+// What a round costs is its chain of dependent memory accesses, so the frontier is kept in LDS with
+// each vertex's first arc and degree: a round is columns, labels, and the row offsets of what it reached.
+// A wave takes up to 64 rows and walks their arcs 64 at a time, whatever their degrees (walk_rows).
 //
 // A graph too large for one workgroup (a batch's largest graphs, or one large high-diameter graph)
 // runs on a team of K workgroups, all resident at once: member m owns a slice of the vertices
-// (its preparation, wake buckets, tail seed and output) and the m-th K-th of every frontier; the
-// next frontier is one shared queue, to which each member appends through a staging buffer in LDS
-// and one reservation per round; the members meet once per round at a barrier in device memory,
-// where the queue's length and the error bits are read.  The labels are then shared by several
-// CUs, so their loads and atomics take device scope.
+// (its preparation, wake buckets, tail seed and output) and a share of every frontier, which is one
+// queue in device memory.  The members meet at a barrier in device memory, where the queue's length
+// and the error bits are read, once per step; a step is one round when the frontier is large or
+// grows fast, else several (see team_step).  The labels are then shared by several CUs, so their
+// loads and atomics take device scope.
 #include "ldd_block.h"
+
+#include <climits>
 
 namespace ldd {
 
@@ -37,33 +39,54 @@ namespace {
 constexpr int BT = 1024;         // threads per workgroup
 constexpr int BNW = BT / WAVE;   // waves per workgroup
 constexpr int WPT = BLOCK_WCAP / BT;  // wake buckets per thread in the scans
-constexpr unsigned TB_CAP = 2048;     // a team member's staged appends per round (more go straight out)
+
+// Frontier entries kept in LDS (double-buffered): alone 12 B each
+// (vertex, first arc, degree), the rest of a larger frontier in the graph's queues; a team member
+// 20 B each (and the label), the rest straight to the team's queue.
+constexpr int LC = 1024;
+constexpr int TC = 2048;
+constexpr int TC1 = TEAM_Q_BYTES / 4;  // a team's step of one round: vertices only
+static_assert(LC * 24 == ALONE_Q_BYTES && TC * 40 == TEAM_Q_BYTES, "the frontier's LDS");
+
+constexpr int LONG_ROW = 32;      // rows of more arcs are taken by a wave at once ...
+constexpr int HUGE_ROW = 4096;    // ... or, above this, listed for the whole workgroup
+constexpr unsigned HCAP = 32;     // such rows listed per round (past that a wave takes them too)
+constexpr int WALK_WORDS = WAVE * LONG_ROW / 64;
+
+struct HeavyRow {
+  u64 offer;
+  int a0, deg;
+};
 
 struct BlockShared {
+  BlockJob j;                // the job in hand
   int woff[BLOCK_WCAP + 1];  // wake bucket offsets (exclusive prefix), then the scatter cursors
-  unsigned pre[BT + 1];      // top-down chunk: exclusive degree prefix
-  int first[BT];             // first arc of each staged entry
-  u64 offer[BT];             // offer of each staged entry
+  u64 starts[BNW][WALK_WORDS];  // per wave: which of its arcs start a row (walk_rows)
+  HeavyRow heavy[HCAP];
   u64 red64[BNW];
   unsigned red32[BNW];
   int job;
   int nxt;                   // next non-empty wake bucket (block minimum)
-  unsigned cnt;              // appends to the next frontier in this round (team, tail)
-  unsigned cnt3[3];          // the same, alone: round k counts in cnt3[k % 3], so one barrier per round
+  unsigned cnt3[3];          // appends: round k counts in cnt3[k % 3], so one barrier per round
+  unsigned nh3[3];           // heavy rows listed, likewise
+  unsigned oc3[3];           // claims: a conflict in the round, likewise
+  unsigned maxdeg;           // alone: the largest degree
   unsigned err;
   u64 delta, n_active;       // preparation results
   u64 settled, examined;     // round results
   long long rounds, sweeps;
   // team of several workgroups on one graph
-  TeamSync* ts;
+  g_sync* ts;
   int tK, tm, tlo, thi;      // team size, this member, this member's vertex slice
   unsigned epoch;            // barriers passed
-  unsigned bn;               // appends staged in tbuf this round
   unsigned tnf;              // the queue length the last team barrier published
   unsigned tcount;           // this member's appends to the shared queue in this step
   unsigned tbase;            // the staged appends' place in the shared queue
+  unsigned spill;            // an append of this step did not fit the LDS before its last round
+  unsigned tspill;           // ... in any member (published by the last barrier)
+  unsigned sfirst;           // vertices this member reached first in this step
+  u64 tfirst;                // ... the team, in the last step
   u64 nz[BLOCK_WCAP / 64];   // non-empty wake buckets of the whole graph
-  int tbuf[TB_CAP];          // staged appends of this member
 };
 
 __device__ __forceinline__ u64 block_max64(u64 v, BlockShared& sh) {
@@ -138,72 +161,50 @@ constexpr int WG = __HIP_MEMORY_SCOPE_WORKGROUP;
 constexpr int AG = __HIP_MEMORY_SCOPE_AGENT;
 
 template <int SC>
-__device__ __forceinline__ u64 lab_load(const u64* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, SC);
+__device__ __forceinline__ u64 lab_load(g_cu64* p) {
+  return __hip_atomic_load(const_cast<g_u64*>(p), __ATOMIC_RELAXED, SC);
 }
 template <int SC>
-__device__ __forceinline__ u64 lab_min(u64* p, u64 v) {
+__device__ __forceinline__ u64 lab_min(g_u64* p, u64 v) {
   return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, SC);
 }
 template <int SC>
-__device__ __forceinline__ void lab_store(u64* p, u64 v) {
+__device__ __forceinline__ void lab_store(g_u64* p, u64 v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, SC);
 }
-__device__ __forceinline__ u64 wg_load(const u64* p) { return lab_load<WG>(p); }
+__device__ __forceinline__ u64 wg_load(g_cu64* p) { return lab_load<WG>(p); }
 
-__device__ __forceinline__ void append(unsigned* cnt, int* next, int v) {
-  const unsigned idx = atomicAdd(cnt, 1u);
-  next[idx] = v;
+// The job in hand (copied to LDS by the kernel), in scalar registers.
+template <class T>
+__device__ __forceinline__ T uniform(T v) {
+  static_assert(sizeof(T) == 8, "a pointer or a 64-bit number");
+  u64 x;
+  __builtin_memcpy(&x, &v, 8);
+  x = (u64)(unsigned)__builtin_amdgcn_readfirstlane((int)x) |
+      (u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
+  __builtin_memcpy(&v, &x, 8);
+  return v;
 }
-
-// Appends to the next frontier.  Alone: counted in LDS, written at once.  step() is called by
-// every thread after each pass of at most BT appends (nothing to do here).
-struct LocalAppend {
-  unsigned* cnt;
-  int* next;
-  __device__ __forceinline__ void operator()(int v) const { append(cnt, next, v); }
-  __device__ __forceinline__ void step() const {}
-};
-
-// The staged appends of a team member go to the team's shared queue behind one reservation
-// (all threads call; `c` entries staged, c <= TB_CAP).
-__device__ __forceinline__ void team_flush(BlockShared& sh, int* next, u64* gcnt, unsigned c) {
-  if (threadIdx.x == 0) {
-    sh.tbase = (unsigned)__hip_atomic_fetch_add(gcnt, (u64)c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sh.tcount += c;
-  }
-  __syncthreads();
-  for (unsigned i = threadIdx.x; i < c; i += BT)
-    __hip_atomic_store(&next[sh.tbase + i], sh.tbuf[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (threadIdx.x == 0) sh.bn = 0;
-  __syncthreads();
+__device__ __forceinline__ BlockJob job_of(const BlockShared& sh) {
+  const BlockJob& s = sh.j;
+  BlockJob j;
+  j.n = __builtin_amdgcn_readfirstlane(s.n);
+  j.nnz = uniform(s.nnz);
+  j.row_ptr = uniform(s.row_ptr);
+  j.col = uniform(s.col);
+  j.shift = uniform(s.shift);
+  j.centre = uniform(s.centre);
+  j.P = uniform(s.P);
+  j.wk = uniform(s.wk);
+  j.wake = uniform(s.wake);
+  j.q0 = uniform(s.q0);
+  j.q1 = uniform(s.q1);
+  j.tail_den = __builtin_amdgcn_readfirstlane(s.tail_den);
+  j.team = __builtin_amdgcn_readfirstlane(s.team);
+  j.sync = uniform(s.sync);
+  j.deg_cap = __builtin_amdgcn_readfirstlane(s.deg_cap);
+  return j;
 }
-
-// A team member: staged in LDS; after a pass that may leave fewer than BT free entries, the
-// staged entries are placed in the shared queue (step(), uniform: one reservation per 1024 or
-// more appends), and the rest at the end of the round.  An append past the staging capacity
-// (which the passes never reach) would reserve its own slot.
-struct TeamAppend {
-  BlockShared* sh;
-  int* next;
-  u64* gcnt;
-  __device__ __forceinline__ void operator()(int v) const {
-    const unsigned i = atomicAdd(&sh->bn, 1u);
-    if (i < TB_CAP) {
-      sh->tbuf[i] = v;
-    } else {
-      __hip_atomic_store(&next[__hip_atomic_fetch_add(gcnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)], v,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      atomicAdd(&sh->tcount, 1u);
-    }
-  }
-  __device__ __forceinline__ void step() const {
-    __syncthreads();
-    const unsigned c = sh->bn;
-    if (c > TB_CAP - BT) team_flush(*sh, next, gcnt, c < TB_CAP ? c : TB_CAP);
-  }
-};
 
 // The slice loops (preparation, wake sort, output) are latency-bound with one vertex per thread at a
 // time: a thread takes VU vertices at once (v, v + BT, ...), and in the output AU arcs of each,
@@ -237,8 +238,8 @@ __device__ __forceinline__ void slice_load(const int* __restrict__ rp, const lon
 // in LDS; the vertices' own labels ((Delta - shift[v]) << B) | v go to wk[lo ...] in bucket order
 // (a wake then needs no shift load) and sh.woff[q] is bucket q's offset from lo (all threads call).
 __device__ __forceinline__ void wake_sort(const BlockJob& j, BlockShared& sh, int lo, int hi, u64 delta) {
-  const int* __restrict__ rp = j.row_ptr;
-  const long long* __restrict__ shift = j.shift;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_ci64* __restrict__ shift = j.shift;
   const int tid = threadIdx.x;
   const int B = j.n > 1 ? 32 - __builtin_clz((unsigned)(j.n - 1)) : 1;
   for (int q = tid; q <= BLOCK_WCAP; q += BT) sh.woff[q] = 0;
@@ -303,9 +304,9 @@ __device__ __forceinline__ void prepare_scan(const BlockJob& j, BlockShared& sh,
                                              u64* dmax_out, u64* active_out, u64* degmax_out = nullptr) {
   const int n = j.n;
   const long long nnz = j.nnz;
-  const int* __restrict__ rp = j.row_ptr;
-  const long long* __restrict__ shift = j.shift;
-  u64* P = j.P;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_ci64* __restrict__ shift = j.shift;
+  g_u64* P = j.P;
   const int tid = threadIdx.x;
   unsigned err = 0;
   u64 dmax = 0, active = 0, degmax = 0;
@@ -354,108 +355,568 @@ __device__ __forceinline__ unsigned range_err(int n, u64 delta) {
 
 // Preparation of one graph: checks, Delta, the vertices with arcs, labels INF, and the wake
 // buckets.  Results in sh (delta, n_active, err, woff).
-__device__ __attribute__((noinline)) void block_prepare(const BlockJob& j, BlockShared& sh) {
+__device__ __attribute__((noinline)) void block_prepare(BlockShared& sh) {
+  const BlockJob j = job_of(sh);
   if (threadIdx.x == 0) sh.err = 0;
   __syncthreads();
-  u64 delta, n_active;
-  prepare_scan(j, sh, 0, j.n, true, &delta, &n_active);
+  u64 delta, n_active, degmax;
+  prepare_scan(j, sh, 0, j.n, true, &delta, &n_active, &degmax);
   if (threadIdx.x == 0) {
     unsigned e = sh.err;
     if (!e) e = range_err(j.n, delta);
     sh.err = e;
     sh.delta = delta;
     sh.n_active = n_active;
+    sh.maxdeg = (unsigned)degmax;
   }
   __syncthreads();
   if (sh.err) return;
   wake_sort(j, sh, 0, j.n, delta);
 }
 
-// Relax the arcs of a staged chunk (ne entries: first arc, degree prefix, offer in LDS; total
-// arcs): every arc offers its entry's label plus one unit to its far end (atomic minimum).  A
-// round appends a far end reached for the first time (old label INF); a tail sweep appends a far
-// end whose label dropped, once per sweep (its stamp takes the sweep's tag).  U arcs per thread
-// are issued together (entries by binary search in LDS, column ids, far labels, minima); one at a
-// time measured fastest (more in flight cost registers and did not pay on batches or small graphs).
-template <int SC, bool SWEEP, class App>
-__device__ __forceinline__ void relax_chunk(const BlockJob& j, BlockShared& sh, unsigned ne, unsigned total, int tag,
-                                            const App& app) {
-  constexpr int U = 1;
-  const int n = j.n;
-  const long long nnz = j.nnz;
-  const int* __restrict__ col = j.col;
-  u64* P = j.P;
-  const int top = ne > 1 ? 1 << (31 - __builtin_clz(ne - 1)) : 0;
-  for (unsigned b0 = 0; b0 < total; b0 += U * BT) {  // the same passes in every thread (app.step)
-    const unsigned base = b0 + threadIdx.x;
-    int w[U];
-    u64 off[U];
+// The LDS of frontiers and small graphs.  A fixed array: the address of dynamic LDS is not a constant
+// outside the kernel's own body, and every access of these functions loaded it from memory first.
+__shared__ __attribute__((aligned(16))) unsigned char blk_dyn[BLOCK_LDS_BYTES];
+
+// Two consecutive row offsets as one access (4-byte aligned).
+struct __attribute__((packed, aligned(4))) RowEnds {
+  int a0, a1;
+};
+__device__ __forceinline__ void row_of(g_cint* rp, int v, int* a0, int* deg) {
+  const RowEnds e = *reinterpret_cast<const LDD_GLOBAL RowEnds*>(rp + v);
+  *a0 = e.a0;
+  *deg = e.a1 - e.a0;
+}
+
+// One row's arcs first, first + stride, ..., two at a time.
+template <class Arcs>
+__device__ __forceinline__ void walk_row(const BlockJob& j, BlockShared& sh, int a0, int deg, u64 o, int first, int stride,
+                                         const Arcs& arcs) {
+  const u64 offer[2] = {o, o};
+#pragma unroll 1
+  for (int x = first; x < deg; x += 2 * stride) {
+    int w[2];
+    bool go[2], bad = false;
+    go[0] = true;
+    go[1] = x + stride < deg;
+    w[0] = j.col[a0 + x];
+    w[1] = go[1] ? j.col[a0 + x + stride] : 0;
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const unsigned a = base + (unsigned)k * BT;
-      int lo = 0;  // last entry with pre <= a (steps from the largest power of two below ne)
-      for (int step = top; step >= 1; step >>= 1)
-        if (lo + step < (int)ne && sh.pre[lo + step] <= a) lo += step;
-      const long long arc = (long long)sh.first[lo] + (a - sh.pre[lo]);
-      w[k] = a < total ? (arc < nnz ? col[arc] : -1) : -2;
-      off[k] = sh.offer[lo];
+    for (int k = 0; k < 2; ++k) {
+      bad |= go[k] && (unsigned)w[k] >= (unsigned)j.n;
+      go[k] = go[k] && (unsigned)w[k] < (unsigned)j.n;
     }
-    u64 pw[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const bool ok = (unsigned)w[k] < (unsigned)n;
-      if (!ok && w[k] != -2) atomicOr(&sh.err, ERR_BAD_COL);
-      pw[k] = ok ? wg_load(&P[w[k]]) : 0;
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      if (pw[k] > off[k]) {
-        const u64 old = lab_min<SC>(&P[w[k]], off[k]);
-        if (SWEEP) {
-          if (old > off[k] && __hip_atomic_exchange(&j.wake[w[k]], tag, __ATOMIC_RELAXED, SC) != tag) app(w[k]);
-        } else if (old == INF) {
-          app(w[k]);
-        }
-      }
-    }
-    app.step();
+    if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+    arcs.template run<2>(w, go, offer);
   }
 }
 
-// Relax the arcs of frontier entries cur[e0 .. e1), staged in LDS a chunk of BT entries at a time
-// (all threads call).
-template <int SC, bool SWEEP, class App>
-__device__ __forceinline__ u64 expand_frontier(const BlockJob& j, BlockShared& sh, const int* cur, unsigned e0,
-                                               unsigned e1, u64 unit, int tag, const App& app) {
-  const int* __restrict__ rp = j.row_ptr;
-  u64 examined = 0;
-  for (unsigned c0 = e0; c0 < e1; c0 += BT) {
-    const unsigned e = c0 + threadIdx.x;
-    unsigned deg = 0;
-    if (e < e1) {
-      // a team's queue entries and offers: device-scope loads (the round's barrier invalidates nothing)
-      int u;
-      if constexpr (SC == AG) u = __hip_atomic_load(const_cast<int*>(&cur[e]), __ATOMIC_RELAXED, AG);
-      else u = cur[e];
-      if (SC == WG || (unsigned)u < (unsigned)j.n) {  // a team's entries are checked (never out of range)
-        const u64 pu = SC == AG ? lab_load<AG>(&j.P[u]) : wg_load(&j.P[u]);
-        const int a0 = rp[u], a1 = rp[u + 1];
-        deg = (unsigned)(a1 - a0);
-        sh.first[threadIdx.x] = a0;
-        sh.offer[threadIdx.x] = pu + unit;
-      } else {
-        atomicOr(&sh.err, ERR_QUEUE);
+// U passes of 64 of a wave's arcs, from word c0 of its start bits on (see walk_rows).
+template <int U, class Arcs>
+__device__ __forceinline__ void walk_pass(const BlockJob& j, BlockShared& sh, const u64* starts, int c0, int total, int& row,
+                                          int adj, u64 offer, const Arcs& arcs) {
+  int w[U];
+  bool go[U], bad = false;
+  u64 off[U];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const u64 word = (c0 + k) * 64 < total ? starts[c0 + k] : 0;
+    const int t = (c0 + k) * 64 + (int)lane_id();
+    // the arc's row: the row starts at or before it
+    const int r = row + (int)rank_below(word) + (int)((word >> lane_id()) & 1) - 1;
+    row += __builtin_popcount(__builtin_amdgcn_readfirstlane((int)word)) +
+           __builtin_popcount(__builtin_amdgcn_readfirstlane((int)(word >> 32)));
+    const int at = __shfl(adj, r, WAVE);
+    off[k] = shfl_u64(offer, r);
+    go[k] = t < total && at != INT_MIN;
+    w[k] = go[k] ? j.col[at + t] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    bad |= go[k] && (unsigned)w[k] >= (unsigned)j.n;
+    go[k] = go[k] && (unsigned)w[k] < (unsigned)j.n;
+  }
+  if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+  arcs.template run<U>(w, go, off);
+}
+
+// The frontier's nf rows.  What bounds this is instructions: with a lane (or eight) per row half of the lanes
+// idle on uneven degrees, and each instruction of a wave costs its SIMD four cycles whether they do or not
+// (RGG with 200,000 vertices, 1400 rows: 18 us a round with eight lanes per row).  So a wave takes up
+// to 64 rows, one per lane, and walks their arcs 64 at a time: a bit per arc in LDS marks where a row starts,
+// and an arc's row is the number of bits up to it.  Neighbouring lanes read neighbouring columns.
+// entry(i) gives row i's first arc, degree and offer; arcs.run gets U far ends per lane with their
+// offers.  Few rows are spread over all waves, from the last one down (the round's wake runs in
+// the first).  A row of more than LONG_ROW arcs is walked by its wave alone, one of more than HUGE_ROW listed in slot
+// ci for walk_heavy.  Rows lie in [0, nnz] (checked by the preparation); columns are checked here.
+template <class Entry, class Arcs>
+__device__ __forceinline__ void walk_rows(const BlockJob& j, BlockShared& sh, int ci, unsigned nf, const Entry& entry,
+                                          const Arcs& arcs, unsigned& examined) {
+  const unsigned lane = lane_id(), wid = BNW - 1 - threadIdx.x / WAVE;
+  const unsigned per = (nf + BNW - 1) / BNW, rows = per < (unsigned)WAVE ? per : (unsigned)WAVE;  // rows per wave and pass
+  u64* starts = sh.starts[wid];
+  for (unsigned i0 = wid * rows; i0 < nf; i0 += BNW * rows) {
+    int a0 = 0, deg = 0;
+    u64 offer = 0;
+    const bool mine = lane < rows && i0 + lane < nf;
+    if (mine) entry(i0 + lane, &a0, &deg, &offer);
+    examined += (unsigned)deg;
+    bool alone = deg > LONG_ROW;
+    if (deg > HUGE_ROW) {
+      const unsigned h = atomicAdd(&sh.nh3[ci], 1u);
+      if (h < HCAP) {
+        sh.heavy[h] = HeavyRow{offer, a0, deg};
+        alone = false;
+        deg = 0;
       }
     }
-    unsigned total;
-    const unsigned ex = block_excl_scan(deg, sh, &total);
-    sh.pre[threadIdx.x] = ex;
-    __syncthreads();
-    examined += threadIdx.x == 0 ? total : 0;
-    relax_chunk<SC, SWEEP>(j, sh, e1 - c0 < (unsigned)BT ? e1 - c0 : (unsigned)BT, total, tag, app);
+    for (u64 m = __ballot(alone); m; m &= m - 1) {
+      const int src = __ffsll((long long)m) - 1;
+      walk_row(j, sh, __builtin_amdgcn_readlane(a0, src), __builtin_amdgcn_readlane(deg, src), shfl_u64(offer, src), (int)lane,
+               WAVE, arcs);
+    }
+    // rows taken elsewhere keep one arc, which is skipped (so that every row has a start)
+    const bool none = alone || deg == 0;
+    const int d = mine ? (none ? 1 : deg) : 0;
+    const int incl = (int)wave_incl_scan((unsigned)d), pre = incl - d;
+    const int total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+    if (lane < (unsigned)WALK_WORDS) starts[lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (mine) atomicOr(reinterpret_cast<unsigned*>(starts) + (pre >> 5), 1u << (pre & 31));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int adj = none ? INT_MIN : a0 - pre;
+    int row = 0;
+    if (total <= 64) {
+      walk_pass<1>(j, sh, starts, 0, total, row, adj, offer, arcs);
+    } else {
+#pragma unroll 1
+      for (int c = 0; c * 64 < total; c += 4) walk_pass<4>(j, sh, starts, c, total, row, adj, offer, arcs);
+    }
+  }
+}
+
+// The rows listed in slot ci, each by the whole workgroup (all threads call, after a barrier; ends
+// without one).
+template <class Arcs>
+__device__ __forceinline__ void walk_heavy(const BlockJob& j, BlockShared& sh, int ci, const Arcs& arcs) {
+  const unsigned nh = sh.nh3[ci] < HCAP ? sh.nh3[ci] : HCAP;
+#pragma unroll 1
+  for (unsigned h = 0; h < nh; ++h) {
+    const HeavyRow e = sh.heavy[h];
+    walk_row(j, sh, e.a0, e.deg, e.offer, (int)threadIdx.x, BT, arcs);
+  }
+}
+
+// Offers applied to the labels in memory.  filter: a far end's label is loaded first and the atomic is left
+// out when it cannot drop; without it the chain is one access shorter, which pays while few rows
+// are in flight.  Every label that may have dropped goes to won(w, first arc of w, degree of w, old
+// label, offer); EAGER: w's row offsets are read while the atomic is in flight (else 0, 0).
+template <int SC, bool EAGER, class Won>
+struct Relax {
+  const BlockJob& j;
+  bool filter;
+  const Won& won;
+  template <int U>
+  __device__ __forceinline__ void run(const int (&w)[U], const bool (&in)[U], const u64 (&offer)[U]) const {
+    u64 pw[U], old[U];
+    int b0[U], bd[U];
+    bool go[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) pw[k] = filter && in[k] ? wg_load(&j.P[w[k]]) : INF;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      go[k] = in[k] && pw[k] > offer[k];
+      b0[k] = bd[k] = 0;
+      if (go[k]) {
+        old[k] = lab_min<SC>(&j.P[w[k]], offer[k]);
+        if (EAGER) row_of(j.row_ptr, w[k], &b0[k], &bd[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (go[k]) won(w[k], b0[k], bd[k], old[k], offer[k]);
+  }
+};
+constexpr unsigned FILTER_MIN = 128;  // frontiers of more rows load the label first
+
+// A frontier's entries in LDS: buffer b of v (vertex), a (first arc), d (degree), and l (label).
+template <int CAP>
+struct Frontier {
+  __device__ static u64& l(int b, int i) { return reinterpret_cast<u64*>(blk_dyn)[b * CAP + i]; }
+  template <int OFF>
+  __device__ static int& at(int b, int i) { return reinterpret_cast<int*>(blk_dyn + OFF)[b * CAP + i]; }
+};
+struct AloneQ : Frontier<LC> {
+  __device__ static int& v(int b, int i) { return at<0>(b, i); }
+  __device__ static int& a(int b, int i) { return at<8 * LC>(b, i); }
+  __device__ static int& d(int b, int i) { return at<16 * LC>(b, i); }
+};
+struct TeamQ : Frontier<TC> {
+  __device__ static int& v(int b, int i) { return at<16 * TC>(b, i); }
+  __device__ static int& a(int b, int i) { return at<24 * TC>(b, i); }
+  __device__ static int& d(int b, int i) { return at<32 * TC>(b, i); }
+  // a step of one round stages vertices only, in all of it
+  __device__ static int& one(unsigned i) { return reinterpret_cast<int*>(blk_dyn)[i]; }
+};
+
+// ---- rounds of a workgroup alone on labels in memory (more than CLAIM_N vertices, and the tail) -----
+// Appends to the next frontier: the first LC entries in LDS (buffer b), the rest in
+// `next` (at most one entry per vertex: n are enough).
+struct AloneAppend {
+  unsigned* cnt;
+  g_int* next;
+  int b;
+  __device__ __forceinline__ void operator()(int v, int a0, int deg) const {
+    const unsigned i = atomicAdd(cnt, 1u);
+    if (i < (unsigned)LC) {
+      AloneQ::v(b, (int)i) = v;
+      AloneQ::a(b, (int)i) = a0;
+      AloneQ::d(b, (int)i) = deg;
+    } else {
+      next[i - LC] = v;
+    }
+  }
+};
+
+// One round (or tail sweep): the wake bucket wk[0 .. nw) and the nf entries of the
+// frontier (buffer b, then cur) offer their labels; what they reach goes to `app`.  A round appends a
+// vertex reached for the first time (old label INF); a sweep one whose label dropped, once per sweep
+// (its stamp takes the sweep's tag).  All threads call; ends with a barrier.
+template <bool SWEEP>
+__device__ __forceinline__ unsigned alone_round(const BlockJob& j, BlockShared& sh, g_cu64* wk, int nw, unsigned nf, int b,
+                                                g_cint* cur, u64 mask, u64 unit, int tag, int ci, const AloneAppend& app) {
+  unsigned examined = 0;
+  const auto won = [&](int w, int a0, int deg, u64 old, u64 offer) {
+    if (SWEEP) {
+      if (old > offer && __hip_atomic_exchange(&j.wake[w], tag, __ATOMIC_RELAXED, WG) != tag) app(w, a0, deg);
+    } else if (old == INF) {
+      app(w, a0, deg);
+    }
+  };
+  const Relax<WG, true, decltype(won)> relax{j, nf > FILTER_MIN, won}, heavy{j, true, won};
+  for (int t = (int)threadIdx.x; t < nw; t += BT) {  // a load first: a vertex reached with a smaller label needs no atomic
+    const u64 self = wk[t];
+    const int v = (int)(self & mask);
+    if (wg_load(&j.P[v]) > self) {
+      int a0, deg;
+      const u64 old = lab_min<WG>(&j.P[v], self);
+      row_of(j.row_ptr, v, &a0, &deg);
+      if (old == INF) app(v, a0, deg);
+    }
+  }
+  walk_rows(
+      j, sh, ci, nf,
+      [&](unsigned i, int* a0, int* deg, u64* offer) {
+        int v;
+        if (i < (unsigned)LC) {
+          v = AloneQ::v(b, (int)i);
+          *a0 = AloneQ::a(b, (int)i);
+          *deg = AloneQ::d(b, (int)i);
+        } else {
+          v = cur[i - LC];
+          row_of(j.row_ptr, v, a0, deg);
+        }
+        *offer = wg_load(&j.P[v]) + unit;
+      },
+      relax, examined);
+  __syncthreads();
+  if (sh.nh3[ci]) {
+    walk_heavy(j, sh, ci, heavy);
     __syncthreads();
   }
   return examined;
+}
+
+// Whether the label-correcting tail takes over: few vertices are left, many rounds remain, and the frontier
+// is small against what is left.  A frontier that still moves reaches it in a few more rounds, for less than
+// the tail's sweeps (256^3 grid, beta 0.02: 4.5 ms with the tail entered at an eighth of what is left, 4.1 ms
+// at a 64th); what is left once it has died down are small components, each waking in its own round.
+constexpr int TAIL_MIN_LEFT = 16;
+constexpr u64 TAIL_IDLE = 64;
+
+__device__ __forceinline__ bool tail_next(const BlockJob& j, u64 n_active, u64 settled, unsigned nf, int left_rounds) {
+  const u64 left = n_active - settled;
+  return j.tail_den > 0 && left > 0 && left * (u64)j.tail_den <= n_active && left_rounds > TAIL_MIN_LEFT &&
+         (u64)nf * TAIL_IDLE <= left;
+}
+// A workgroup alone pays the tail's scan of every vertex against rounds of about 2.5 us each.
+constexpr int TAIL_SCAN = 4096;
+
+// ---- rounds of a workgroup alone, claimed in LDS --------------------------------------------
+// Global atomics bound a workgroup's rounds: a 64-bit atomic minimum costs a CU 1.7 ns alone and 9.4 ns
+// when every CU issues them (27 G/s over the GPU, whatever the scope and size), a load from L2
+// 0.5 - 1 ns.  So a graph of at most CLAIM_N vertices keeps two bits per vertex in LDS, "settled before
+// this round" and "reached": an arc to a settled vertex costs no memory access beyond its column, and
+// the first offer to a vertex is seen without asking its label.  The offers of a round meet in a
+// direct-mapped table in LDS.  They all lie in one round, so an entry is 56 bits: the vertex, and below
+// it the fraction and centre of its smallest offer; one LDS minimum enters an offer.  Of two
+// vertices of one slot the larger loses it and takes a second slot, whose loser goes to its label in memory
+// by an atomic minimum (a conflict).  When the round ends its vertices' labels are written once, with plain stores.
+// A round whose frontier outweighs the vertices left, of a graph without long rows, pulls instead:
+// each unsettled vertex reads its row, tests its neighbours' frontier bits in LDS and loads the labels
+// of those in the frontier (no atomics).
+constexpr int TABLE = 4096;     // slots for CLAIM_N vertices (twice as many fit beside the bits of half as many)
+constexpr int FC = 2048;        // entries of the frontier kept in LDS; the rest in the graph's queue
+constexpr int PULL_DEG = 64;    // pull only when no vertex has more arcs
+constexpr unsigned PULL_MIN = 2048, PULL_X = 3;  // pull when frontier > PULL_MIN and > unsettled / PULL_X
+constexpr int LOW = 38;         // bits of a fraction and a centre: 20 + 18
+constexpr int PULL_U = 8;       // arcs a pulling lane has in flight
+constexpr int PULL_WIN = 8192;  // vertices listed at a time in a pull
+
+struct ClaimLds {  // LDS: the frontier, the table, the vertices' bits
+  static constexpr int FL = 0, FV = FL + 8 * FC, FA = FV + 4 * FC, FD = FA + 4 * FC, TAB = FD + 4 * FC,
+                       END = TAB + 8 * TABLE + CLAIM_N / 4;
+  static_assert(END == CLAIM_Q_BYTES && CLAIM_N <= 1 << (LOW - FIX), "the frontier's LDS");
+  static_assert(CLAIM_N / 8 <= 8 * TABLE && 2 * PULL_WIN <= 8 * FC, "a pull's bits and list take the table's and labels' place");
+  // the bits from the end down, so that their place does not depend on the table's size
+  __device__ static unsigned& bits(unsigned i) { return reinterpret_cast<unsigned*>(blk_dyn + END)[~(int)i]; }
+  __device__ static u64& tab(unsigned i) { return reinterpret_cast<u64*>(blk_dyn + TAB)[i]; }
+  __device__ static unsigned& fbits(unsigned i) { return reinterpret_cast<unsigned*>(blk_dyn + TAB)[i]; }
+  __device__ static u64& fl(unsigned i) { return reinterpret_cast<u64*>(blk_dyn + FL)[i]; }  // frontier: label,
+  __device__ static int& fv(unsigned i) { return reinterpret_cast<int*>(blk_dyn + FV)[i]; }  // vertex (of the next one,
+  __device__ static int& fa(unsigned i) { return reinterpret_cast<int*>(blk_dyn + FA)[i]; }  // while it is built),
+  __device__ static int& fd(unsigned i) { return reinterpret_cast<int*>(blk_dyn + FD)[i]; }  // first arc, degree
+  __device__ static unsigned short& list(unsigned i) { return reinterpret_cast<unsigned short*>(blk_dyn + FL)[i]; }
+};
+constexpr unsigned REACHED = 1, SETTLED = 2;
+
+__device__ __forceinline__ unsigned vertex_bits(unsigned v) { return ClaimLds::bits(v >> 4) >> ((v & 15) * 2) & 3u; }
+static_assert(TABLE == 1 << 12, "Claim::shift");
+static_assert(8 * TABLE == CLAIM_N / 8, "twice the slots beside the bits of half the vertices");
+
+struct Claim {  // what a round's offers need
+  g_u64* P;
+  g_int* over;     // the next frontier's entries past FC
+  unsigned* cnt;   // its length
+  unsigned* conf;  // set by a conflict
+  u64 base;        // the round's first label
+  int shift;       // 32 - log2 of the table's slots
+  __device__ __forceinline__ unsigned slot(unsigned v) const { return v * 2654435761u >> shift; }
+  __device__ __forceinline__ unsigned slot2(unsigned v) const { return v * 2246822519u >> shift; }
+  __device__ __forceinline__ void reach(int w) const {
+    const unsigned i = atomicAdd(cnt, 1u);
+    if (i < (unsigned)FC) ClaimLds::fv(i) = w;
+    else over[i - FC] = w;
+  }
+  // the offer's place in the table; what it pushed out (or met) when the slot is another vertex's
+  __device__ __forceinline__ u64 enter(int w, u64 offer) const {
+    return atomicMin(&ClaimLds::tab(slot((unsigned)w)), (u64)w << LOW | (offer - base));
+  }
+  // the loser of a shared slot takes its vertex's second slot; the loser of that one goes to memory
+  __device__ __forceinline__ void place_loser(int w, u64 offer, u64 old) const {
+    if (old == INF || (int)(old >> LOW) == w) return;
+    const u64 mine = (u64)w << LOW | (offer - base);
+    u64 lost = mine > old ? mine : old;
+    const unsigned v = (unsigned)(lost >> LOW);
+    const u64 second = atomicMin(&ClaimLds::tab(slot2(v)), lost);
+    if (second == INF || (unsigned)(second >> LOW) == v) return;
+    lost = lost > second ? lost : second;
+    (void)lab_min<WG>(&P[lost >> LOW], base + (lost & (((u64)1 << LOW) - 1)));
+    *conf = 1;
+  }
+};
+
+struct ClaimArcs {  // offers along arcs, to their unsettled far ends
+  const Claim& c;
+  template <int U>
+  __device__ __forceinline__ void run(const int (&w)[U], const bool (&in)[U], const u64 (&offer)[U]) const {
+    unsigned f[U];
+    u64 old[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) f[k] = in[k] ? vertex_bits((unsigned)w[k]) : SETTLED;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      old[k] = INF;
+      if (!(f[k] & SETTLED)) old[k] = c.enter(w[k], offer[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      if (f[k] == 0) {
+        const unsigned s = ((unsigned)w[k] & 15) * 2;
+        if (!(atomicOr(&ClaimLds::bits((unsigned)w[k] >> 4), REACHED << s) >> s & REACHED)) c.reach(w[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) c.place_loser(w[k], offer[k], old[k]);
+  }
+};
+
+// A round's offers: the wake bucket wk[0 .. nw) and the frontier's nf entries, the first FC in LDS, the rest
+// in cur.  All threads call; ends with a barrier.
+__device__ __forceinline__ unsigned claim_round(const BlockJob& j, BlockShared& sh, const Claim& c, g_cu64* wk, int nw,
+                                                unsigned nf, g_cint* cur, u64 mask, u64 unit, int ci) {
+  unsigned examined = 0;
+  const ClaimArcs arcs{c};
+  for (int t = (int)threadIdx.x; t < nw; t += BT) {
+    const u64 self[1] = {wk[t]};
+    const int v[1] = {(int)(self[0] & mask)};
+    const bool in[1] = {true};
+    arcs.run<1>(v, in, self);
+  }
+  walk_rows(
+      j, sh, ci, nf,
+      [&](unsigned i, int* a0, int* deg, u64* offer) {
+        if (i < (unsigned)FC) {
+          *a0 = ClaimLds::fa(i);
+          *deg = ClaimLds::fd(i);
+          *offer = ClaimLds::fl(i) + unit;
+        } else {
+          const int v = cur[i - FC];
+          row_of(j.row_ptr, v, a0, deg);
+          *offer = wg_load(&j.P[v]) + unit;
+        }
+      },
+      arcs, examined);
+  __syncthreads();
+  if (sh.nh3[ci]) {
+    walk_heavy(j, sh, ci, arcs);
+    __syncthreads();
+  }
+  return examined;
+}
+
+__device__ __forceinline__ void table_clear(int slots) {
+  for (int i = threadIdx.x; i < slots; i += BT) ClaimLds::tab((unsigned)i) = INF;
+}
+
+// A pulled round: the wake bucket's unsettled vertices take their own labels, then every unsettled
+// vertex the best offer of its neighbours in the frontier.  Labels go straight to memory (a conflict, for
+// the settling).  All threads call; ends with a barrier.
+__device__ __forceinline__ u64 pull_round(const BlockJob& j, BlockShared& sh, const Claim& c, g_cu64* wk, int nw, unsigned nf,
+                                          g_cint* cur, u64 mask, u64 unit) {
+  const int n = j.n;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_cint* __restrict__ col = j.col;
+  g_u64* P = j.P;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < (n + 31) / 32; i += BT) ClaimLds::fbits((unsigned)i) = 0;
+  for (int t = tid; t < nw; t += BT) {
+    const u64 self = wk[t];
+    const unsigned v = (unsigned)(self & mask);
+    if (!(vertex_bits(v) & SETTLED)) lab_store<WG>(&P[v], self);  // INF until now
+  }
+  __syncthreads();
+  for (unsigned i = tid; i < nf; i += BT) {
+    const unsigned v = (unsigned)(i < (unsigned)FC ? ClaimLds::fv(i) : cur[i - FC]);
+    atomicOr(&ClaimLds::fbits(v >> 5), 1u << (v & 31));
+  }
+  if (tid == 0) *c.conf = 1;
+  u64 examined = 0;
+  for (int v0 = 0; v0 < n; v0 += PULL_WIN) {  // the window's unsettled vertices are listed, then pull
+    __syncthreads();
+    if (tid == 0) sh.nxt = 0;
+    __syncthreads();
+    const int hi = n - v0 < PULL_WIN ? n - v0 : PULL_WIN;
+    for (int i = tid; i < hi; i += BT)
+      if (!(vertex_bits((unsigned)(v0 + i)) & SETTLED))
+        ClaimLds::list((unsigned)atomicAdd(&sh.nxt, 1)) = (unsigned short)i;
+    __syncthreads();
+    const int cnt = sh.nxt;
+    for (int i = tid; i < cnt; i += BT) {
+      const int v = v0 + ClaimLds::list((unsigned)i);
+      const int a0 = rp[v], a1 = rp[v + 1];
+      if (a0 == a1) continue;
+      const u64 p = wg_load(&P[v]);
+      u64 best = p;
+      examined += (u64)(a1 - a0);
+      for (int a = a0; a < a1; a += PULL_U) {
+        int w[PULL_U];
+        u64 pw[PULL_U];
+        bool bad = false;
+#pragma unroll
+        for (int k = 0; k < PULL_U; ++k) w[k] = a + k < a1 ? col[a + k] : v;  // (v is not in the frontier)
+#pragma unroll
+        for (int k = 0; k < PULL_U; ++k) {
+          const bool ok = (unsigned)w[k] < (unsigned)n;
+          bad |= !ok;
+          const bool in = ok && ((ClaimLds::fbits((unsigned)w[k] >> 5) >> (w[k] & 31)) & 1u);
+          pw[k] = in ? wg_load(&P[w[k]]) + unit : INF;
+        }
+#pragma unroll
+        for (int k = 0; k < PULL_U; ++k) best = pw[k] < best ? pw[k] : best;
+        if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+      }
+      if (best < p) lab_store<WG>(&P[v], best);
+      if (best != INF) c.reach(v);
+    }
+  }
+  __syncthreads();
+  table_clear(1 << (32 - c.shift));
+  __syncthreads();
+  return examined;
+}
+
+// The rounds of one prepared graph of at most CLAIM_N vertices until all are settled or the tail may
+// start (returned), with the state of block_rounds.
+__device__ __forceinline__ bool claim_rounds(const BlockJob& j, BlockShared& sh, g_int* cur, g_int* next, int& r, u64& settled,
+                                             u64& examined, long long& rounds) {
+  const int n = j.n;
+  g_u64* P = j.P;
+  const int tid = threadIdx.x;
+  const int shift = n <= CLAIM_N / 2 ? 19 : 20;
+  const u64 delta = sh.delta, n_active = sh.n_active;
+  const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
+  const int D = (int)(delta >> FIX);
+  const u64 unit = (u64)1 << (FIX + B), mask = ((u64)1 << B) - 1;
+  for (int i = tid; i < (n + 15) / 16; i += BT) ClaimLds::bits((unsigned)i) = 0;
+  table_clear(1 << (32 - shift));
+  if (tid < 3) sh.oc3[tid] = 0;
+  __syncthreads();
+  unsigned nf = 0;
+  int ci = 0;
+  while (settled < n_active && r <= D + n && rounds <= (long long)D + n + 2) {
+    const int w0 = r <= D ? sh.woff[r] : 0, nw = r <= D ? sh.woff[r + 1] - w0 : 0;
+    const Claim c{P, next, &sh.cnt3[ci], &sh.oc3[ci], (u64)r << (FIX + B), shift};
+    if (nf > PULL_MIN && sh.maxdeg <= PULL_DEG && (u64)nf * PULL_X > n_active - settled)
+      examined += pull_round(j, sh, c, j.wk + w0, nw, nf, cur, mask, unit);
+    else
+      examined += claim_round(j, sh, c, j.wk + w0, nw, nf, cur, mask, unit, ci);
+    // the round's vertices are settled: their labels to memory, their rows to the frontier's entries
+    nf = sh.cnt3[ci];
+    const bool conf = sh.oc3[ci] != 0;
+    for (unsigned i = tid; i < nf; i += BT) {
+      const unsigned v = (unsigned)(i < (unsigned)FC ? ClaimLds::fv(i) : next[i - FC]);
+      const unsigned h1 = c.slot(v), h2 = c.slot2(v);
+      const u64 t1 = ClaimLds::tab(h1), t2 = ClaimLds::tab(h2);
+      int a0, deg;
+      row_of(j.row_ptr, (int)v, &a0, &deg);
+      const u64 seen = conf ? wg_load(&P[v]) : INF;
+      u64 t = INF;
+      if ((unsigned)(t1 >> LOW) == v) {
+        t = t1;
+        ClaimLds::tab(h1) = INF;
+      }
+      if ((unsigned)(t2 >> LOW) == v) {
+        t = t2 < t ? t2 : t;
+        ClaimLds::tab(h2) = INF;
+      }
+      u64 p = t == INF ? INF : c.base + (t & (((u64)1 << LOW) - 1));
+      if (p < seen) lab_store<WG>(&P[v], p);
+      else p = seen;
+      atomicOr(&ClaimLds::bits(v >> 4), (SETTLED | REACHED) << ((v & 15) * 2));
+      if (i < (unsigned)FC) {
+        ClaimLds::fl(i) = p;
+        ClaimLds::fa(i) = a0;
+        ClaimLds::fd(i) = deg;
+      }
+    }
+    if (tid == 0) {
+      const int old = ci == 0 ? 2 : ci - 1;
+      sh.cnt3[old] = sh.oc3[old] = sh.nh3[old] = 0;
+    }
+    __syncthreads();
+    ci = ci == 2 ? 0 : ci + 1;
+    if (sh.err) break;
+    settled += nf;
+    ++rounds;
+    g_int* t = cur;
+    cur = next;
+    next = t;
+    if (nf) ++r;
+    else r = next_nonempty(sh, r + 1, D);
+    if (tail_next(j, n_active, settled, nf, D - r - n / TAIL_SCAN)) return true;
+  }
+  return false;
 }
 
 // The rounds of one prepared graph (results in sh: settled, examined, rounds, sweeps, err).
@@ -465,62 +926,70 @@ __device__ __forceinline__ u64 expand_frontier(const BlockJob& j, BlockShared& s
 // whose offers are still pending), then sweeps relax the changed labels until none drops.  The
 // labels are the unique fixpoint of P(v) = min(own label, min_w P(w) + unit), so the result is
 // the same exact one.
-constexpr int TAIL_MIN_LEFT = 16;
-
-__device__ __attribute__((noinline)) void block_rounds(const BlockJob& j, BlockShared& sh) {
+__device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
+  const BlockJob j = job_of(sh);
   const int n = j.n;
-  const int* __restrict__ rp = j.row_ptr;
-  const int* __restrict__ col = j.col;
-  const long long* __restrict__ shift = j.shift;
-  u64* P = j.P;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_cint* __restrict__ col = j.col;
+  g_ci64* __restrict__ shift = j.shift;
+  g_u64* P = j.P;
   const int tid = threadIdx.x;
   const u64 delta = sh.delta, n_active = sh.n_active;
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const int D = (int)(delta >> FIX);
   const u64 unit = (u64)1 << (FIX + B);
-  int* cur = j.q0;
-  int* next = j.q1;
+  g_int* cur = j.q0;
+  g_int* next = j.q1;
+  int b = 0;  // the frontier's buffer in LDS
   unsigned nf = 0;
   u64 settled = 0, examined = 0;
   long long rounds = 0, sweeps = 0;
   const u64 mask = ((u64)1 << B) - 1;
-  if (tid < 3) sh.cnt3[tid] = 0;
-  int ci = 0;  // this round's append counter: cnt3[ci]; cnt3[(ci + 2) % 3] is cleared for two rounds on
+  if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
+  int ci = 0;  // this round's counters: cnt3[ci], nh3[ci]; those of (ci + 2) % 3 are cleared for two rounds on
   int r = next_nonempty(sh, 0, D);
   bool tail = false;
-  while (settled < n_active && r <= D + n && rounds <= (long long)D + n + 2) {  // r past the end: stop
-    unsigned* cnt = &sh.cnt3[ci];
-    const int w0 = r <= D ? sh.woff[r] : 0, w1 = r <= D ? sh.woff[r + 1] : 0;
-    // wake bucket r: each vertex offers its own label (a load first: a vertex reached earlier with
-    // a smaller label needs no atomic)
-    for (int i = w0 + tid; i < w1; i += BT) {
-      const u64 self = j.wk[i];
-      const int v = (int)(self & mask);
-      if (wg_load(&P[v]) > self && lab_min<WG>(&P[v], self) == INF) append(cnt, next, v);
+  // after a round's barrier: its appends are the frontier; the counters of round k - 1 (read by every
+  // thread before that barrier) are cleared for round k + 2
+  const auto advance = [&]() {
+    nf = sh.cnt3[ci];
+    if (tid == 0) {
+      const int old = ci == 0 ? 2 : ci - 1;
+      sh.cnt3[old] = 0;
+      sh.nh3[old] = 0;
     }
-    examined += expand_frontier<WG, false>(j, sh, cur, 0, nf, unit, 0, LocalAppend{cnt, next});
-    __syncthreads();  // this round's appends are done; every thread has read the count of round k - 1
-    nf = *cnt;
-    if (tid == 0) sh.cnt3[ci == 0 ? 2 : ci - 1] = 0;  // round k - 1's counter, next used by round k + 2
     ci = ci == 2 ? 0 : ci + 1;
+    g_int* t = cur;
+    cur = next;
+    next = t;
+    b ^= 1;
+  };
+  const bool claims = n <= CLAIM_N;
+  if (claims) {
+    tail = claim_rounds(j, sh, cur, next, r, settled, examined, rounds);
+    __syncthreads();
+    if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
+    __syncthreads();
+  }
+  while (!claims && settled < n_active && r <= D + n && rounds <= (long long)D + n + 2) {
+    const int w0 = r <= D ? sh.woff[r] : 0, w1 = r <= D ? sh.woff[r + 1] : 0;
+    const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
+    examined += alone_round<false>(j, sh, j.wk + w0, w1 - w0, nf, b, cur, mask, unit, 0, ci, app);
+    advance();
     if (sh.err) break;
     settled += nf;
     ++rounds;
-    int* t = cur;
-    cur = next;
-    next = t;
     if (nf) ++r;
     else r = next_nonempty(sh, r + 1, D);
-    const u64 left = n_active - settled;
-    if (j.tail_den > 0 && left > 0 && left * (u64)j.tail_den <= n_active && D - r > TAIL_MIN_LEFT) {
+    if (tail_next(j, n_active, settled, nf, D - r - n / TAIL_SCAN)) {
       tail = true;
       break;
     }
   }
   if (tail && !sh.err) {
-    // seed: F_{r-1} is cur (nf entries, final labels); every unreached vertex with arcs takes the
-    // best of its own label and its neighbours' in F_{r-1}, and is queued for the first sweep
-    unsigned* cnt = &sh.cnt3[ci];
+    // seed: F_{r-1} is the frontier (final labels); every unreached vertex with arcs takes the best of
+    // its own label and its neighbours' in F_{r-1}, and is queued for the first sweep
+    const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
     const u64 prev_round = (u64)(r - 1);
     for (int v = tid; v < n; v += BT) {
       const int a0 = rp[v], a1 = rp[v + 1];
@@ -538,27 +1007,16 @@ __device__ __attribute__((noinline)) void block_rounds(const BlockJob& j, BlockS
       examined += (u64)(a1 - a0);
       lab_store<WG>(&P[v], best);
       j.wake[v] = -1;  // the stamp of the first sweep
-      append(cnt, next, v);
+      app(v, a0, a1 - a0);
     }
     __syncthreads();
-    nf = *cnt;
-    if (tid == 0) sh.cnt3[ci == 0 ? 2 : ci - 1] = 0;
-    ci = ci == 2 ? 0 : ci + 1;
-    int* t = cur;
-    cur = next;
-    next = t;
+    advance();
     // sweeps: sweep k relaxes the labels queued by the step before and queues those that drop
     for (int k = 1; nf && !sh.err && sweeps <= n; ++k) {
-      unsigned* cnt = &sh.cnt3[ci];
-      examined += expand_frontier<WG, true>(j, sh, cur, 0, nf, unit, -(k + 1), LocalAppend{cnt, next});
-      __syncthreads();
-      nf = *cnt;
-      if (tid == 0) sh.cnt3[ci == 0 ? 2 : ci - 1] = 0;
-      ci = ci == 2 ? 0 : ci + 1;
+      const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
+      examined += alone_round<true>(j, sh, nullptr, 0, nf, b, cur, mask, unit, -(k + 1), ci, app);
+      advance();
       ++sweeps;
-      t = cur;
-      cur = next;
-      next = t;
     }
     settled = n_active;
   }
@@ -573,15 +1031,17 @@ __device__ __attribute__((noinline)) void block_rounds(const BlockJob& j, BlockS
   __syncthreads();
 }
 
-// Centres (INF: an isolated vertex, its own centre) and the cut, from the final labels.
 // Centres and cut arcs of the vertices [lo, hi), added to *cut2 and *pieces; an arc to a vertex out
-// of range (arcs of the last frontier were not read by a round) sets ERR_BAD_COL.
+// of range (arcs of the last frontier were not read by a round) sets ERR_BAD_COL.  The graph is symmetric, so
+// an edge is looked at from its smaller end alone and counts as two arcs: the far ends' labels are what
+// bounds this pass (random accesses: with every CU busy 2.3 ns an arc, half of a random graph's
+// whole time, when both arcs loaded one).
 __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh, int lo, int hi, u64 mask, u64* cut2,
                                              u64* pieces) {
   const int n = j.n;
-  const int* __restrict__ rp = j.row_ptr;
-  const int* __restrict__ col = j.col;
-  const u64* P = j.P;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_cint* __restrict__ col = j.col;
+  g_cu64* P = j.P;
   for (int v0 = lo + (int)threadIdx.x; v0 < hi; v0 += VU * BT) {
     int a[VU], a1[VU], c[VU];
     u64 p[VU];
@@ -605,6 +1065,7 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
         *pieces += c[k] == v;
       }
     }
+    bool bad = false;
     for (bool more = true; more;) {  // AU arcs of each vertex per pass
       int w[VU][AU];
       bool has[VU][AU];
@@ -619,36 +1080,101 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
 #pragma unroll
       for (int k = 0; k < VU; ++k)
 #pragma unroll
-        for (int t = 0; t < AU; ++t) pw[k][t] = has[k][t] && (unsigned)w[k][t] < (unsigned)n ? wg_load(&P[w[k][t]]) : 0;
+        for (int t = 0; t < AU; ++t) {
+          const bool ok = (unsigned)w[k][t] < (unsigned)n;
+          bad |= has[k][t] && !ok;
+          has[k][t] = has[k][t] && ok && w[k][t] > v0 + k * BT;
+          pw[k][t] = has[k][t] ? wg_load(&P[w[k][t]]) : 0;
+        }
       more = false;
 #pragma unroll
       for (int k = 0; k < VU; ++k) {
 #pragma unroll
-        for (int t = 0; t < AU; ++t) {
-          if (!has[k][t]) continue;
-          if ((unsigned)w[k][t] >= (unsigned)n) {
-            atomicOr(&sh.err, ERR_BAD_COL);
-            a1[k] = a[k];
-            break;
-          }
-          const int cw = pw[k][t] == INF ? w[k][t] : (int)(pw[k][t] & mask);
-          *cut2 += cw != c[k];
-        }
+        for (int t = 0; t < AU; ++t)
+          *cut2 += has[k][t] && (pw[k][t] == INF ? w[k][t] : (int)(pw[k][t] & mask)) != c[k] ? 2u : 0u;
         a[k] += AU;
         more |= a[k] < a1[k];
+      }
+    }
+    if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+  }
+}
+
+// The same with the centres (at most 16 bits) kept in LDS.  Centres of the vertices [lo, hi) (INF: an isolated vertex, its own
+// centre), four per thread at a time; put(v, centre) is called for each.
+template <class Put>
+__device__ __forceinline__ void output_centres(const BlockJob& j, int lo, int hi, u64 mask, u64* pieces, const Put& put) {
+  for (int v0 = lo + (int)threadIdx.x; v0 < hi; v0 += VU * BT) {
+    u64 p[VU];
+#pragma unroll
+    for (int k = 0; k < VU; ++k) p[k] = v0 + k * BT < hi ? wg_load(&j.P[v0 + k * BT]) : 0;
+#pragma unroll
+    for (int k = 0; k < VU; ++k) {
+      const int v = v0 + k * BT;
+      if (v < hi) {
+        const int c = p[k] == INF ? v : (int)(p[k] & mask);
+        j.centre[v] = c;
+        *pieces += c == v;
+        put(v, c);
       }
     }
   }
 }
 
-__device__ __attribute__((noinline)) void block_output(const BlockJob& j, BlockShared& sh, BlockOut* out) {
+// Arcs of the rows [lo, hi) whose ends have different centres (of(v): v's centre, known once
+// output_centres is done), added to *cut2.  An arc to a vertex out of range (arcs of the last frontier were
+// not read by a round) sets ERR_BAD_COL.  The rows are walked as a frontier's: a lane per row took 0.94 ns an
+// arc, most of it idle lanes on uneven degrees.
+template <class Of>
+struct CutArcs {
+  const Of& of;
+  u64& cut2;
+  template <int U>
+  __device__ __forceinline__ void run(const int (&w)[U], const bool (&in)[U], const u64 (&c)[U]) const {
+    int cw[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) cw[k] = in[k] ? of(w[k]) : 0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) cut2 += in[k] && cw[k] != (int)c[k];
+  }
+};
+template <class Of>
+__device__ __forceinline__ void output_cut(const BlockJob& j, BlockShared& sh, int lo, int hi, const Of& of, u64* cut2) {
+  if (threadIdx.x == 0) sh.nh3[0] = 0;
+  __syncthreads();
+  const CutArcs<Of> arcs{of, *cut2};
+  unsigned examined = 0;
+  walk_rows(
+      j, sh, 0, (unsigned)(hi - lo),
+      [&](unsigned i, int* a0, int* deg, u64* c) {
+        row_of(j.row_ptr, lo + (int)i, a0, deg);
+        *c = (u64)(unsigned)of(lo + (int)i);
+      },
+      arcs, examined);
+  __syncthreads();
+  walk_heavy(j, sh, 0, arcs);
+}
+
+__device__ __attribute__((noinline)) void block_output(BlockShared& sh, BlockOut* out) {
+  const BlockJob j = job_of(sh);
   const int n = j.n;
   const int tid = threadIdx.x;
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const u64 mask = ((u64)1 << B) - 1;
   const unsigned e0 = sh.err | (sh.settled < sh.n_active ? ERR_WATCHDOG : 0u);
   u64 cut2 = 0, pieces = 0;
-  if (!e0) output_slice(j, sh, 0, n, mask, &cut2, &pieces);
+  if (!e0) {
+    // centres of up to 16 bits are kept in LDS (a load from L2 costs a CU 0.5 - 1 ns), others read as written
+    unsigned short* lc = reinterpret_cast<unsigned short*>(blk_dyn);
+    static_assert(CLAIM_Q_BYTES >= 2 << 16, "centres in LDS");
+    if (n <= 1 << 16) {
+      output_centres(j, 0, n, mask, &pieces, [&](int v, int c) { lc[v] = (unsigned short)c; });
+      __syncthreads();
+      output_cut(j, sh, 0, n, [&](int v) { return (int)lc[v]; }, &cut2);
+    } else {
+      output_slice(j, sh, 0, n, mask, &cut2, &pieces);
+    }
+  }
   cut2 = block_sum64(cut2, sh);
   pieces = block_sum64(pieces, sh);
   if (tid == 0) {
@@ -663,11 +1189,9 @@ __device__ __attribute__((noinline)) void block_output(const BlockJob& j, BlockS
   }
 }
 
-extern __shared__ __attribute__((aligned(16))) unsigned char blk_dyn[];  // the launch's dynamic LDS
-
 // One graph, the whole workgroup.
-__device__ void block_graph(const BlockJob& j, BlockShared& sh, BlockOut* out) {
-  block_prepare(j, sh);
+__device__ void block_graph(BlockShared& sh, BlockOut* out) {
+  block_prepare(sh);
   if (sh.err) {
     if (threadIdx.x == 0) {
       out->err = sh.err;
@@ -675,28 +1199,11 @@ __device__ void block_graph(const BlockJob& j, BlockShared& sh, BlockOut* out) {
     }
     return;
   }
-  block_rounds(j, sh);
-  block_output(j, sh, out);
+  block_rounds(sh);
+  block_output(sh, out);
 }
 
-// One small graph, the whole workgroup, with its labels, wake order and queues in the dynamic LDS
-// (P: 8 B, wake order: 8 B, queues: 2 x 4 B per vertex); the same code reaches them through
-// generic pointers.  The labels are copied to the graph's label array at the end.
-__device__ void block_graph_lds(const BlockJob& j, BlockShared& sh, BlockOut* out) {
-  const int n = j.n;
-  BlockJob l = j;
-  u64* base = reinterpret_cast<u64*>(blk_dyn);
-  l.P = base;
-  l.wk = base + n;
-  l.wake = reinterpret_cast<int*>(l.wk);
-  l.q0 = reinterpret_cast<int*>(base + 2 * (long long)n);
-  l.q1 = l.q0 + n;
-  block_graph(l, sh, out);
-  __syncthreads();
-  for (int v = threadIdx.x; v < n; v += BT) j.P[v] = l.P[v];
-}
-
-// One small graph whose labels and CSR fit the dynamic LDS, the whole workgroup: every vertex
+// One small graph whose labels and CSR fit the LDS, the whole workgroup: every vertex
 // starts from its own label ((Delta - shift) << B) | v and the labels are relaxed,
 // P(v) = min(P(v), min over arcs (v, u) of P(u) + unit), in place, until a pass lowers none.
 // That is the unique fixpoint the rounds reach (the minimum over centres of the shifted
@@ -707,12 +1214,13 @@ __device__ void block_graph_lds(const BlockJob& j, BlockShared& sh, BlockOut* ou
 // centre, plus one block of passes (fewer, since labels lowered early in a pass are read later in
 // the same pass).
 // Labels are 8-byte LDS words written whole, so a concurrent read sees the old or the new label.
-__device__ __attribute__((noinline)) void block_graph_fix(const BlockJob& j, BlockShared& sh, BlockOut* out) {
+__device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, BlockOut* out) {
+  const BlockJob j = job_of(sh);
   const int n = j.n;
   const long long nnz = j.nnz;
-  const int* __restrict__ rp = j.row_ptr;
-  const int* __restrict__ col = j.col;
-  const long long* __restrict__ shift = j.shift;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_cint* __restrict__ col = j.col;
+  g_ci64* __restrict__ shift = j.shift;
   const int tid = threadIdx.x;
   u64* P = reinterpret_cast<u64*>(blk_dyn);
   int* lrp = reinterpret_cast<int*>(P + n);
@@ -827,22 +1335,24 @@ __device__ __forceinline__ void team_clear_next(BlockShared& sh) {
   if (threadIdx.x == 0) {
     __hip_atomic_store(&sh.ts->tw[nx].v, 0ull, __ATOMIC_RELAXED, AG);
     __hip_atomic_store(&sh.ts->qcnt[nx], 0ull, __ATOMIC_RELAXED, AG);
+    __hip_atomic_store(&sh.ts->first[nx], 0ull, __ATOMIC_RELAXED, AG);
   }
 }
 
 // The team's barrier k (all threads call; k = sh.epoch, slot k % 3).  Every wave first waits for
 // its own stores and atomics to complete (a workgroup barrier does not wait for other waves'
-// stores to leave the CU).  Then thread 0 arrives, adding (1 << 42) | (error ? 1 << 32 : 0) | (its
-// appends this step) to its group's word; the group's last arrival adds the group's sums to the
-// team's word, and the team's last arrival publishes the step's queue length (the sum of the
-// appends; 0xffffffff if any member had an error) with the barrier's number in gen, which the
-// others wait for.  In a team of at most TEAM_GROUP members the arrivals go to the team's word
-// directly.  full: arrivals are acquire-release read-modify-writes, gen a release store and the
-// wait ends with an acquire, so every plain write of the members before the barrier is visible to
-// plain loads after it (each member writes back and invalidates its L2).  Otherwise everything is
-// relaxed: the members' shared accesses are device-scope themselves and complete before the
-// arrival (the waits above), and every load after the barrier is issued after the wait observed
-// gen.  A bounded wait raises ERR_BARRIER instead of hanging.  Returns the queue length; after an
+// stores to leave the CU).  Then thread 0 arrives, adding (1 << 44) | (spill ? 1 << 38 : 0) |
+// (error ? 1 << 32 : 0) | (its appends this step) to its group's word; the group's last arrival adds
+// the group's sums to the team's word, and the team's last arrival publishes the step's queue length
+// (the sum of the appends, bit 31: some member spilled; 0xffffffff if any member had an error) with the
+// barrier's number in gen, which the others wait for.  In a team of at most TEAM_GROUP members the
+// arrivals go to the team's word directly.  full: arrivals are acquire-release read-modify-writes,
+// gen a release store and the wait ends with an acquire, so every plain write of the members before
+// the barrier is visible to plain loads after it (each member writes back and invalidates its L2).
+// Otherwise everything is relaxed: the members' shared accesses are device-scope themselves and
+// complete before the arrival (the waits above), and every load after the barrier is issued after
+// the wait observed gen.  A bounded wait raises ERR_BARRIER instead of hanging.  Returns the queue
+// length (and in sh.tspill, sh.tfirst the step's spill and the vertices it reached first); after an
 // error every member ORs the team's error bits into sh.err.
 template <bool FULL>
 __device__ unsigned team_barrier(BlockShared& sh) {
@@ -852,33 +1362,36 @@ __device__ unsigned team_barrier(BlockShared& sh) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x == 0) {
-    TeamSync* ts = sh.ts;
+    g_sync* ts = sh.ts;
     const unsigned K = (unsigned)sh.tK, g = (unsigned)sh.tm / TEAM_GROUP;
     const unsigned ng = (K + TEAM_GROUP - 1) / TEAM_GROUP;
     const unsigned in_g = K - g * TEAM_GROUP < (unsigned)TEAM_GROUP ? K - g * TEAM_GROUP : (unsigned)TEAM_GROUP;
     const unsigned e1 = sh.epoch + 1;
     const int slot = (int)(sh.epoch % 3);
     if (sh.err) __hip_atomic_fetch_or(&ts->err, sh.err, __ATOMIC_RELAXED, AG);
-    constexpr u64 ONE = 1ull << 42, SUMS = ONE - 1;
-    const u64 mine = ONE | (sh.err ? 1ull << 32 : 0ull) | (u64)sh.tcount;
+    constexpr int ARR = 44, SPILL = 38, ERR = 32;  // at most 32 groups or members: six bits each
+    const u64 mine = (1ull << ARR) | ((u64)(sh.spill != 0) << SPILL) | ((u64)(sh.err != 0) << ERR) | (u64)sh.tcount;
+    const auto bits = [](u64 sum) {  // one error and one spill whatever their count
+      return (sum & 0xffffffffu) | ((u64)(((sum >> ERR) & 63) != 0) << ERR) | ((u64)(((sum >> SPILL) & 63) != 0) << SPILL);
+    };
     bool last = false;
     u64 sum = 0;
     if (ng == 1) {
       const u64 old = __hip_atomic_fetch_add(&ts->tw[slot].v, mine, RMW, AG);
-      last = (old >> 42) + 1 == K;
-      sum = (old & SUMS) + (mine & SUMS);
+      last = (old >> ARR) + 1 == K;
+      sum = bits(old + mine);
     } else {
       const u64 old = __hip_atomic_fetch_add(&ts->gw[slot][g].v, mine, RMW, AG);
-      if ((old >> 42) + 1 == in_g) {
-        const u64 grp = ONE | ((old & SUMS) + (mine & SUMS));
+      if ((old >> ARR) + 1 == in_g) {
+        const u64 grp = (1ull << ARR) | bits(old + mine);
         const u64 top = __hip_atomic_fetch_add(&ts->tw[slot].v, grp, RMW, AG);
-        last = (top >> 42) + 1 == ng;
-        sum = (top & SUMS) + (grp & SUMS);
+        last = (top >> ARR) + 1 == ng;
+        sum = bits(top + grp);
       }
     }
     u64 word;
     if (last) {
-      const unsigned nf = (sum >> 32) ? 0xffffffffu : (unsigned)sum;
+      const unsigned nf = ((sum >> ERR) & 1) ? 0xffffffffu : (unsigned)sum | (unsigned)((sum >> SPILL) & 1) << 31;
       word = ((u64)nf << 32) | e1;
       __hip_atomic_store(&ts->gen, word, PUB, AG);
     } else {
@@ -894,27 +1407,60 @@ __device__ unsigned team_barrier(BlockShared& sh) {
     }
     if (FULL) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     unsigned nf = (unsigned)(word >> 32);
+    sh.tspill = 0;
     if (nf == 0xffffffffu) {
       const unsigned e = __hip_atomic_load(&ts->err, __ATOMIC_RELAXED, AG);
       sh.err |= e ? e : (unsigned)ERR_BARRIER;
       nf = 0;
+    } else {
+      sh.tspill = nf >> 31;
+      nf &= 0x7fffffffu;
     }
+    sh.tfirst = __hip_atomic_load(&ts->first[slot], __ATOMIC_RELAXED, AG);
     sh.tnf = nf;
     sh.tcount = 0;
+    sh.spill = 0;
     sh.epoch = e1;
   }
   __syncthreads();
   return sh.tnf;
 }
 
-// End of a member's step: its staged appends go to the shared queue `next`, then the barrier,
-// which returns the queue's length, the same in every member (all threads call).
-template <bool FULL>
-__device__ unsigned team_round_end(BlockShared& sh, int* next, u64* gcnt) {
+// The c entries staged in LDS (buffer b; ONE: of a step of one round) go to the team's shared queue behind
+// one reservation (all threads call; ends with a barrier).  Entries past the queue's n are dropped with
+// BLK_QUEUE.
+template <bool ONE>
+__device__ __forceinline__ void team_flush(BlockShared& sh, int n, g_int* next, g_u64* gcnt, int b, unsigned c) {
+  if (threadIdx.x == 0) {
+    sh.tbase = (unsigned)__hip_atomic_fetch_add(gcnt, (u64)c, __ATOMIC_RELAXED, AG);
+    sh.tcount += c;
+  }
   __syncthreads();
-  const unsigned c = sh.bn < TB_CAP ? sh.bn : TB_CAP;
-  if (c) team_flush(sh, next, gcnt, c);
-  return team_barrier<FULL>(sh);
+  const unsigned base = sh.tbase;
+  for (unsigned i = threadIdx.x; i < c; i += BT) {
+    const int v = ONE ? TeamQ::one(i) : TeamQ::v(b, (int)i);
+    if (base + i < (unsigned)n) __hip_atomic_store(&next[base + i], v, __ATOMIC_RELAXED, AG);
+    else atomicOr(&sh.err, BLK_QUEUE);
+  }
+  __syncthreads();
+}
+
+// End of a member's step: what its last round staged (buffer b, cnt entries counted) goes to the shared
+// queue `next`, then the barrier, which returns the queue's length, the same in every member (all
+// threads call, after a barrier).
+template <bool FULL, bool ONE>
+__device__ __forceinline__ unsigned team_step_end(BlockShared& sh, int n, g_int* next, g_u64* gcnt, int b, unsigned cnt) {
+  constexpr unsigned CAP = ONE ? TC1 : TC;
+  const unsigned c = cnt < CAP ? cnt : CAP;
+  if (threadIdx.x == 0 && sh.sfirst) {
+    __hip_atomic_fetch_add(&sh.ts->first[sh.epoch % 3], (u64)sh.sfirst, __ATOMIC_RELAXED, AG);
+    sh.sfirst = 0;
+  }
+  if (c) team_flush<ONE>(sh, n, next, gcnt, b, c);
+  const unsigned nf = team_barrier<FULL>(sh);
+  if (threadIdx.x < 3) sh.cnt3[threadIdx.x] = sh.nh3[threadIdx.x] = 0;
+  __syncthreads();
+  return nf;
 }
 
 // Before plain loads of labels that other members wrote since the last full barrier: an acquire
@@ -947,12 +1493,14 @@ __device__ __forceinline__ int team_next_nonempty(BlockShared& sh, int r, int D)
 // Team preparation: every member scans its slice (checks, labels INF, Delta and the vertices with
 // arcs, combined by atomics in the team's record) and sorts its slice's wake buckets; the members'
 // non-empty buckets are ORed into the record and read back after a second barrier.
-__device__ __attribute__((noinline)) void team_prepare(const BlockJob& j, BlockShared& sh) {
+__device__ __attribute__((noinline)) void team_prepare(BlockShared& sh) {
+  const BlockJob j = job_of(sh);
   const int tid = threadIdx.x;
-  TeamSync* ts = sh.ts;
+  g_sync* ts = sh.ts;
   if (tid == 0) {
     sh.err = 0;
-    sh.bn = 0;
+    sh.spill = 0;
+    sh.sfirst = 0;
   }
   __syncthreads();
   u64 dmax, active, degmax;
@@ -991,72 +1539,294 @@ __device__ __attribute__((noinline)) void team_prepare(const BlockJob& j, BlockS
   __syncthreads();
 }
 
-// The rounds of a team: the same rounds and tail as block_rounds, with labels at device scope,
-// wakes from the member's slice, expansion of the member's K-th of the frontier, appends to the
-// shared queue, and one barrier per round (or seed, or sweep), which returns the next frontier's
-// length.
-__device__ __attribute__((noinline)) void team_rounds(const BlockJob& j, BlockShared& sh) {
+// What a team member reaches in a round: staged in LDS (ONE: TC1 vertices; else TC entries of buffer b), the
+// rest straight to the team's queue, each behind its own reservation (an entry past the queue's n is
+// dropped with BLK_QUEUE).  early: the entry is expected in LDS by a later round of this step (a spill).
+template <bool ONE>
+struct TeamAppend {
+  BlockShared* sh;
+  unsigned* cnt;
+  g_int* next;
+  g_u64* gcnt;
+  int n, b;
+  bool early;
+  __device__ __forceinline__ void operator()(int v, int a0, int deg, u64 label) const {
+    const unsigned i = atomicAdd(cnt, 1u);
+    if (ONE && i < (unsigned)TC1) {
+      TeamQ::one(i) = v;
+      return;
+    }
+    if (!ONE && i < (unsigned)TC) {
+      TeamQ::v(b, (int)i) = v;
+      TeamQ::a(b, (int)i) = a0;
+      TeamQ::d(b, (int)i) = deg;
+      TeamQ::l(b, (int)i) = label;
+      return;
+    }
+    const u64 at = __hip_atomic_fetch_add(gcnt, 1ull, __ATOMIC_RELAXED, AG);
+    if (at < (u64)n) __hip_atomic_store(&next[at], v, __ATOMIC_RELAXED, AG);
+    else atomicOr(&sh->err, BLK_QUEUE);
+    atomicAdd(&sh->tcount, 1u);
+    if (early) sh->spill = 1;
+  }
+};
+
+// The wake of round r in a team member: the vertices of its own bucket offer their labels (lane t of nw).
+template <class Won>
+__device__ __forceinline__ void team_wake(const BlockJob& j, g_cu64* wk, u64 mask, const Won& won) {
+  const u64 self = *wk;
+  const int v = (int)(self & mask);
+  if (wg_load(&j.P[v]) > self) {  // a load first: a vertex reached earlier with a smaller label needs no atomic
+    const u64 old = lab_min<AG>(&j.P[v], self);
+    int a0, deg;
+    row_of(j.row_ptr, v, &a0, &deg);
+    won(v, a0, deg, old, self);
+  }
+}
+
+// Entry cur[i] of the shared queue: its row, and its label plus `unit` (device-scope loads: the team's
+// relaxed barrier invalidates nothing).
+__device__ __forceinline__ void team_entry(const BlockJob& j, BlockShared& sh, g_cint* cur, unsigned i, u64 unit, int* a0,
+                                           int* deg, u64* offer) {
+  const int u = __hip_atomic_load(const_cast<g_int*>(&cur[i]), __ATOMIC_RELAXED, AG);
+  *a0 = *deg = 0;
+  *offer = 0;
+  if ((unsigned)u < (unsigned)j.n) {
+    *offer = lab_load<AG>(&j.P[u]) + unit;
+    row_of(j.row_ptr, u, a0, deg);
+  } else {
+    atomicOr(&sh.err, ERR_QUEUE);
+  }
+}
+
+// A step of one round (or tail sweep) of a team member: its bucket of round r wakes, and its share [e0, e1) of
+// the frontier is relaxed.  first_only: the frontier is final, so a vertex is appended when it is reached
+// first (its label is final when the round ends, and is read again in the next one), else whenever
+// its label drops.  A sweep appends a vertex once (its stamp takes the tag).  All threads call; returns
+// the queue's length.
+template <bool SWEEP>
+__device__ __attribute__((noinline)) unsigned team_step1(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
+                                                         int r, int D, bool first_only, int tag, u64& examined) {
+  const BlockJob j = job_of(sh);
   const int n = j.n;
-  const int* __restrict__ rp = j.row_ptr;
-  const int* __restrict__ col = j.col;
-  const long long* __restrict__ shift = j.shift;
-  u64* P = j.P;
-  TeamSync* ts = sh.ts;
+  const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
+  const u64 unit = (u64)1 << (FIX + B), mask = ((u64)1 << B) - 1;
+  g_u64* gcnt = &sh.ts->qcnt[sh.epoch % 3];
+  const TeamAppend<true> app{&sh, &sh.cnt3[0], nxt, gcnt, n, 0, false};
+  unsigned firsts = 0, ex = 0;
+  const auto won = [&](int w, int a0, int deg, u64 old, u64 offer) {
+    firsts += old == INF;
+    if (SWEEP) {
+      if (old > offer && __hip_atomic_exchange(&j.wake[w], tag, __ATOMIC_RELAXED, AG) != tag) app(w, a0, deg, offer);
+    } else if (first_only ? old == INF : old > offer) {
+      app(w, a0, deg, offer);
+    }
+  };
+  const Relax<AG, false, decltype(won)> relax{j, e1 - e0 > FILTER_MIN, won}, heavy{j, true, won};
+  if (!SWEEP && r <= D) {
+    const int w1 = sh.woff[r + 1];
+    for (int t = sh.woff[r] + (int)threadIdx.x; t < w1; t += BT) team_wake(j, j.wk + sh.tlo + t, mask, won);
+  }
+  for (unsigned c0 = e0; c0 < e1; c0 += BT) {  // BT rows at a time: the staging has room for what they reach
+    const unsigned cn = e1 - c0 < (unsigned)BT ? e1 - c0 : (unsigned)BT;
+    walk_rows(
+        j, sh, 0, cn,
+        [&](unsigned i, int* a0, int* deg, u64* offer) { team_entry(j, sh, cur, c0 + i, unit, a0, deg, offer); }, relax, ex);
+    if (c0 + BT < e1) {
+      __syncthreads();
+      const unsigned c = sh.cnt3[0];
+      if (c > (unsigned)TC1 / 2) {
+        team_flush<true>(sh, n, nxt, gcnt, 0, c < (unsigned)TC1 ? c : (unsigned)TC1);
+        if (threadIdx.x == 0) sh.cnt3[0] = 0;
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  if (sh.nh3[0]) {
+    walk_heavy(j, sh, 0, heavy);
+    __syncthreads();
+  }
+  examined += ex;
+  firsts = (unsigned)wave_sum_u64(firsts);
+  if (lane_id() == 0 && firsts) atomicAdd(&sh.sfirst, firsts);
+  __syncthreads();
+  return team_step_end<false, true>(sh, n, nxt, gcnt, 0, sh.cnt3[0]);
+}
+
+// A step of several rounds r, r + 1, ... (or tail sweeps): the first relaxes the member's share [e0, e1)
+// of the shared frontier, each later one what the member itself lowered in the round before (entries
+// in LDS, with the label they were given); each wakes the member's own bucket of that round.  What the last
+// round lowers goes to the shared queue.  All threads call; returns the queue's length.
+//
+// Several rounds per step are exact.  Claim: a vertex whose final label lies in round r + i gets it
+// from some member in that member's own round i of the step or an earlier one.  A vertex whose own label is
+// the final one wakes in that round in its owner; any other has a neighbour with a final label one
+// round below, whose last lowering queued it with that label in a member that relaxes it one round later
+// at the latest.  So after the step every label below r + rounds is final, as after that many single
+// rounds.  Labels above their final value are passed on too and lowered again later, which costs
+// work, never the result: whoever lowers a label queues the vertex (it may then be queued twice).
+// The claim needs every entry to stay in LDS.  A member whose LDS is full before the last round (a
+// spill) leaves entries to the next step, and the rounds go on as label correction until the queue is
+// empty; offers stay below r + rounds all the same (an entry of the queue lies below r), so no
+// vertex is given a label above its own one before its wake round.
+template <bool SWEEP>
+__device__ __attribute__((noinline)) unsigned team_steps(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
+                                                         int r, int D, int rounds, u64& examined) {
+  const BlockJob j = job_of(sh);
+  const int n = j.n;
+  const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
+  const u64 unit = (u64)1 << (FIX + B), mask = ((u64)1 << B) - 1;
+  g_u64* gcnt = &sh.ts->qcnt[sh.epoch % 3];
+  unsigned firsts = 0, ex = 0;
+  int ci = 0;
+#pragma unroll 1
+  for (int k = 0; k < rounds; ++k) {
+    const int ib = k & 1;  // the LDS buffer read; the other one is written
+    const TeamAppend<false> app{&sh, &sh.cnt3[ci], nxt, gcnt, n, ib ^ 1, k + 1 < rounds};
+    unsigned nin = e1 - e0;
+    if (k) {
+      nin = sh.cnt3[ci == 0 ? 2 : ci - 1];
+      nin = nin < (unsigned)TC ? nin : (unsigned)TC;
+    }
+    const auto won = [&](int w, int a0, int deg, u64 old, u64 offer) {
+      firsts += old == INF;
+      if (old > offer) app(w, a0, deg, offer);
+    };
+    const Relax<AG, true, decltype(won)> relax{j, nin > FILTER_MIN, won};
+    if (!SWEEP && r + k <= D) {
+      const int w1 = sh.woff[r + k + 1];
+      for (int t = sh.woff[r + k] + (int)threadIdx.x; t < w1; t += BT) team_wake(j, j.wk + sh.tlo + t, mask, won);
+    }
+    walk_rows(
+        j, sh, ci, nin,
+        [&](unsigned i, int* a0, int* deg, u64* offer) {
+          if (k) {
+            *a0 = TeamQ::a(ib, (int)i);
+            *deg = TeamQ::d(ib, (int)i);
+            *offer = TeamQ::l(ib, (int)i) + unit;
+          } else {
+            team_entry(j, sh, cur, e0 + i, unit, a0, deg, offer);
+          }
+        },
+        relax, ex);
+    __syncthreads();
+    if (sh.nh3[ci]) {
+      walk_heavy(j, sh, ci, relax);
+      __syncthreads();
+    }
+    if (k + 1 < rounds) {
+      if (threadIdx.x == 0) {  // the counters of the round before, read by every thread: free for round k + 2
+        const int old = ci == 0 ? 2 : ci - 1;
+        sh.cnt3[old] = 0;
+        sh.nh3[old] = 0;
+      }
+      ci = ci == 2 ? 0 : ci + 1;
+    }
+  }
+  examined += ex;
+  firsts = (unsigned)wave_sum_u64(firsts);
+  if (lane_id() == 0 && firsts) atomicAdd(&sh.sfirst, firsts);
+  __syncthreads();
+  return team_step_end<false, false>(sh, n, nxt, gcnt, rounds & 1, sh.cnt3[ci]);
+}
+
+// Rounds per step.  A step of one round costs the team a barrier and the queue's way through device memory
+// (about 6 us in all) beside its rounds' chains (about 3 us each); STEP_MAX rounds share them.  But a
+// member alone relaxes what it reached in the step, so the frontier must not grow fast (a random
+// graph's explosion would stay in few members and overflow their LDS, and reach most vertices by
+// detours) and must fit their LDS: the rounds double while the frontier grows by less than half a step
+// (plus STEP_SLACK entries) and a member's share stays below STEP_SHARE, and halve otherwise.
+// MIN_SHARE: a small frontier is left to fewer members, so that each has a connected patch of it.
+constexpr int STEP_MAX = 8;
+constexpr unsigned STEP_SLACK = 8;
+constexpr unsigned STEP_SHARE = 512;
+constexpr unsigned MIN_SHARE = 32;
+
+__device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K) {
+  if (spill || nf > STEP_SHARE * (unsigned)K) return 1;
+  if (nf <= before + before / 2 + STEP_SLACK) return rounds < STEP_MAX ? 2 * rounds : STEP_MAX;
+  return rounds > 1 ? rounds / 2 : 1;
+}
+
+// The member's share [e0, e1) of a frontier of nf entries.
+__device__ __forceinline__ void team_share(unsigned nf, unsigned K, unsigned m, unsigned* e0, unsigned* e1) {
+  const unsigned want = (nf + MIN_SHARE - 1) / MIN_SHARE, ks = want < K ? want : K;
+  *e0 = m < ks ? (unsigned)((u64)nf * m / ks) : 0u;
+  *e1 = m < ks ? (unsigned)((u64)nf * (m + 1) / ks) : 0u;
+}
+
+// The rounds of a team: the same rounds and tail as block_rounds, in steps of one or more rounds
+// (team_step) with one barrier each.
+__device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
+  const BlockJob j = job_of(sh);
+  const int n = j.n;
+  g_cint* __restrict__ rp = j.row_ptr;
+  g_cint* __restrict__ col = j.col;
+  g_ci64* __restrict__ shift = j.shift;
+  g_u64* P = j.P;
   const int tid = threadIdx.x;
   const int K = sh.tK, m = sh.tm, lo = sh.tlo, hi = sh.thi;
   const u64 delta = sh.delta, n_active = sh.n_active;
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const int D = (int)(delta >> FIX);
   const u64 unit = (u64)1 << (FIX + B);
-  const u64 mask = ((u64)1 << B) - 1;
-  int* cur = j.q0;
-  int* nxt = j.q1;
-  unsigned nf = 0;
+  g_int* cur = j.q0;
+  g_int* nxt = j.q1;
+  unsigned nf = 0, e0, e1;
   u64 settled = 0, examined = 0;
   long long rounds = 0, sweeps = 0;
+  if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
   int r = team_next_nonempty(sh, 0, D);
+  int step = 1;        // rounds of the next step
+  bool clean = true;   // no entry of the queue was left over by a spill
   bool tail = false;
-  while (settled < n_active && r <= D + n && rounds <= (long long)D + n + 2) {
-    u64* gcnt = &ts->qcnt[sh.epoch % 3];
-    const TeamAppend app{&sh, nxt, gcnt};
-    if (r <= D) {
-      const int w0 = sh.woff[r], w1 = sh.woff[r + 1];
-      for (int i0 = w0; i0 < w1; i0 += BT) {  // the same passes in every thread (app.step)
-        const int i = i0 + tid;
-        if (i < w1) {
-          const u64 self = j.wk[lo + i];
-          const int v = (int)(self & mask);
-          if (wg_load(&P[v]) > self && lab_min<AG>(&P[v], self) == INF) app(v);
-        }
-        app.step();
-      }
-    }
-    const unsigned e0 = (unsigned)((u64)nf * m / K), e1 = (unsigned)((u64)nf * (m + 1) / K);
-    examined += expand_frontier<AG, false>(j, sh, cur, e0, e1, unit, 0, app);
-    nf = team_round_end<false>(sh, nxt, gcnt);
+  // at most D / 1 steps wake, and every step moves every queued label one round on
+  for (long long steps = 0; steps <= (long long)D + n + 2; ++steps) {
+    if (settled >= n_active && (clean || nf == 0)) break;
+    if (nf == 0 && r > D) break;
+    team_share(nf, (unsigned)K, (unsigned)m, &e0, &e1);
+    const unsigned before = nf;
+    if (step > 1) nf = team_steps<false>(sh, cur, nxt, e0, e1, r, D, step, examined);
+    else nf = team_step1<false>(sh, cur, nxt, e0, e1, r, D, clean, 0, examined);
     if (sh.err) break;
-    settled += nf;
-    ++rounds;
-    int* t = cur;
+    settled += sh.tfirst;
+    rounds += step;
+    if (sh.tspill) clean = false;
+    g_int* t = cur;
     cur = nxt;
     nxt = t;
-    if (nf) ++r;
-    else r = team_next_nonempty(sh, r + 1, D);
-    const u64 left = n_active - settled;
-    if (j.tail_den > 0 && left > 0 && left * (u64)j.tail_den <= n_active && D - r > TAIL_MIN_LEFT) {
+    r = r > D ? r : r + step;
+    if (nf == 0) {
+      clean = true;
+      r = team_next_nonempty(sh, r, D);
+    }
+    step = next_rounds(step, before, nf, sh.tspill, K);
+    if (tail_next(j, n_active, settled, nf, D - r)) {
       tail = true;
       break;
     }
   }
   if (tail && !sh.err) {
-    // seed over the member's slice (see block_rounds), then sweeps over the shared queue
-    u64* gcnt = &ts->qcnt[sh.epoch % 3];
-    const TeamAppend app{&sh, nxt, gcnt};
-    const u64 prev_round = (u64)(r - 1);
+    // seed over the member's slice (see block_rounds): every unreached vertex takes the best of its own
+    // label and what its reached neighbours offer.  With a clean queue their offers are the only ones
+    // pending (every other neighbour of the frontier is final), else the frontier stays queued too.
+    g_u64* gcnt = &sh.ts->qcnt[sh.epoch % 3];
+    const TeamAppend<true> app{&sh, &sh.cnt3[0], nxt, gcnt, n, 0, false};
     team_acquire();
-    for (int v0 = lo; v0 < hi; v0 += BT) {  // the same passes in every thread (app.step)
+    const auto room = [&]() {  // after each pass of at most BT appends
+      __syncthreads();
+      const unsigned c = sh.cnt3[0];
+      if (c > (unsigned)(TC1 - BT)) {
+        team_flush<true>(sh, n, nxt, gcnt, 0, c < (unsigned)TC1 ? c : (unsigned)TC1);
+        if (tid == 0) sh.cnt3[0] = 0;
+      }
+      __syncthreads();
+    };
+    for (int v0 = lo; v0 < hi; v0 += BT) {  // the same passes in every thread
       const int v = v0 + tid;
       const int a0 = v < hi ? rp[v] : 0, a1 = v < hi ? rp[v + 1] : 0;
+      if (v < hi) j.wake[v] = -1;  // the stamp of the first sweep
       if (a1 > a0 && wg_load(&P[v]) == INF) {
         u64 best = ((delta - (u64)shift[v]) << B) | (u64)v;
         for (int a = a0; a < a1; ++a) {
@@ -1066,28 +1836,34 @@ __device__ __attribute__((noinline)) void team_rounds(const BlockJob& j, BlockSh
             break;
           }
           const u64 pu = wg_load(&P[u]);
-          if (pu != INF && (pu >> (FIX + B)) == prev_round && pu + unit < best) best = pu + unit;
+          if (pu != INF && pu + unit < best) best = pu + unit;
         }
         examined += (u64)(a1 - a0);
         lab_store<AG>(&P[v], best);
-        j.wake[v] = -1;  // the stamp of the first sweep
-        app(v);
+        app(v, 0, 0, 0);
       }
-      app.step();
+      room();
     }
-    nf = team_round_end<true>(sh, nxt, gcnt);
-    int* t = cur;
-    cur = nxt;
-    nxt = t;
-    for (int k = 1; nf && !sh.err && sweeps <= n; ++k) {
-      gcnt = &ts->qcnt[sh.epoch % 3];
-      const unsigned e0 = (unsigned)((u64)nf * m / K), e1 = (unsigned)((u64)nf * (m + 1) / K);
-      examined += expand_frontier<AG, true>(j, sh, cur, e0, e1, unit, -(k + 1), TeamAppend{&sh, nxt, gcnt});
-      nf = team_round_end<false>(sh, nxt, gcnt);
-      ++sweeps;
-      t = cur;
+    if (!clean) {
+      team_share(nf, (unsigned)K, (unsigned)m, &e0, &e1);
+      for (unsigned i0 = e0; i0 < e1; i0 += BT) {
+        const unsigned i = i0 + (unsigned)tid;
+        if (i < e1) app(__hip_atomic_load(&cur[i], __ATOMIC_RELAXED, AG), 0, 0, 0);
+        room();
+      }
+    }
+    nf = team_step_end<true, true>(sh, n, nxt, gcnt, 0, sh.cnt3[0]);
+    step = 1;
+    for (int k = 1; nf && !sh.err && k <= n + 1; ++k) {
+      g_int* t = cur;
       cur = nxt;
       nxt = t;
+      team_share(nf, (unsigned)K, (unsigned)m, &e0, &e1);
+      const unsigned before = nf;
+      if (step > 1) nf = team_steps<true>(sh, cur, nxt, e0, e1, 0, 0, step, examined);
+      else nf = team_step1<true>(sh, cur, nxt, e0, e1, 0, 0, false, -(k + 1), examined);
+      sweeps += step;
+      step = next_rounds(step, before, nf, sh.tspill, K);
     }
     settled = n_active;
   }
@@ -1104,16 +1880,19 @@ __device__ __attribute__((noinline)) void team_rounds(const BlockJob& j, BlockSh
 
 // Centres and cut of the member's slice, summed in the team's record; after a last barrier,
 // member 0 writes the graph's result.
-__device__ __attribute__((noinline)) void team_output(const BlockJob& j, BlockShared& sh, BlockOut* out) {
+__device__ __attribute__((noinline)) void team_output(BlockShared& sh, BlockOut* out) {
+  const BlockJob j = job_of(sh);
   const int n = j.n;
-  TeamSync* ts = sh.ts;
+  g_sync* ts = sh.ts;
   const int tid = threadIdx.x;
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const u64 mask = ((u64)1 << B) - 1;
   const unsigned e0 = sh.err | (sh.settled < sh.n_active ? ERR_WATCHDOG : 0u);
   u64 cut2 = 0, pieces = 0;
   team_acquire();
-  if (!e0) output_slice(j, sh, sh.tlo, sh.thi, mask, &cut2, &pieces);
+  if (!e0) {
+    output_slice(j, sh, sh.tlo, sh.thi, mask, &cut2, &pieces);
+  }
   cut2 = block_sum64(cut2, sh);
   pieces = block_sum64(pieces, sh);
   __syncthreads();
@@ -1137,11 +1916,11 @@ __device__ __attribute__((noinline)) void team_output(const BlockJob& j, BlockSh
 }
 
 // Member m of the graph's team: the slice of 64-aligned vertices it owns, then the three phases.
-__device__ void team_graph(const BlockJob& j, BlockShared& sh, BlockOut* out, int m) {
-  const int n = j.n, K = j.team;
+__device__ void team_graph(BlockShared& sh, BlockOut* out, int m) {
+  const int n = sh.j.n, K = sh.j.team;
   const int chunk = (int)((((long long)n + K - 1) / K + 63) & ~63ll);
   if (threadIdx.x == 0) {
-    sh.ts = j.sync;
+    sh.ts = sh.j.sync;
     sh.tK = K;
     sh.tm = m;
     sh.tlo = (int)min((long long)n, (long long)m * chunk);
@@ -1150,7 +1929,7 @@ __device__ void team_graph(const BlockJob& j, BlockShared& sh, BlockOut* out, in
     sh.tcount = 0;
   }
   __syncthreads();
-  team_prepare(j, sh);
+  team_prepare(sh);
   if (sh.err) {
     if (threadIdx.x == 0 && m == 0) {
       out->err = sh.err;
@@ -1158,8 +1937,8 @@ __device__ void team_graph(const BlockJob& j, BlockShared& sh, BlockOut* out, in
     }
     return;
   }
-  team_rounds(j, sh);
-  team_output(j, sh, out);
+  team_rounds(sh);
+  team_output(sh, out);
 }
 
 }  // namespace
@@ -1174,8 +1953,7 @@ __device__ void team_graph(const BlockJob& j, BlockShared& sh, BlockOut* out, in
 // the team size must not exceed the resident workgroups (the host keeps it within the grid).
 __global__ __launch_bounds__(BT, 4) void k_block_decompose(const BlockJob* __restrict__ jobs,
                                                            const TeamJob* __restrict__ order, int njobs,
-                                                           unsigned* next_job, BlockOut* outs, BlockJob single,
-                                                           int lds_bytes) {
+                                                           unsigned* next_job, BlockOut* outs, BlockJob single) {
   __shared__ BlockShared sh;
   for (;;) {
     int g = 0, m = (int)blockIdx.x;
@@ -1188,12 +1966,12 @@ __global__ __launch_bounds__(BT, 4) void k_block_decompose(const BlockJob* __res
       g = order[k].g;
       m = order[k].m;
     }
-    const BlockJob& j = order ? jobs[g] : single;
+    if (threadIdx.x == 0) sh.j = order ? jobs[g] : single;
+    __syncthreads();
     const u64 t0 = wall_clock64();
-    if (j.team > 1) team_graph(j, sh, &outs[g], m);
-    else if (fix_lds_bytes(j.n, j.nnz) <= lds_bytes) block_graph_fix(j, sh, &outs[g]);
-    else if (rounds_lds_bytes(j.n) <= lds_bytes) block_graph_lds(j, sh, &outs[g]);
-    else block_graph(j, sh, &outs[g]);
+    if (sh.j.team > 1) team_graph(sh, &outs[g], m);
+    else if (fix_lds_bytes(sh.j.n, sh.j.nnz) <= BLOCK_LDS_BYTES) block_graph_fix(sh, &outs[g]);
+    else block_graph(sh, &outs[g]);
     if (threadIdx.x == 0 && m == 0) {
       outs[g].t_begin = t0;
       outs[g].t_end = wall_clock64();
@@ -1224,18 +2002,18 @@ __global__ void k_block_jobs(int G, long long N, const long long* vo, const long
     const long long v0 = vo[g];
     j.n = (int)(vo[g + 1] - v0);
     j.nnz = ao[g + 1] - ao[g];
-    j.row_ptr = row_ptr + v0 + g;
-    j.col = col + ao[g];
-    j.shift = shift + v0;
-    j.centre = centre + v0;
-    j.P = P + v0;
-    j.wk = (u64*)wq + v0;
-    j.wake = (int*)(j.wk);
-    j.q0 = wq + 2 * N + v0;
-    j.q1 = wq + 3 * N + v0;
+    j.row_ptr = (g_cint*)(row_ptr + v0 + g);
+    j.col = (g_cint*)(col + ao[g]);
+    j.shift = (g_ci64*)(shift + v0);
+    j.centre = (g_int*)(centre + v0);
+    j.P = (g_u64*)(P + v0);
+    j.wk = (g_u64*)wq + v0;
+    j.wake = (g_int*)(j.wk);
+    j.q0 = (g_int*)wq + 2 * N + v0;
+    j.q1 = (g_int*)wq + 3 * N + v0;
     j.tail_den = tail_den;
     j.team = team ? team[2 * g] : 1;
-    j.sync = j.team > 1 ? sync + team[2 * g + 1] : nullptr;
+    j.sync = j.team > 1 ? (g_sync*)(sync + team[2 * g + 1]) : nullptr;
     j.deg_cap = 0;
     jobs[g] = j;
   }
