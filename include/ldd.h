@@ -76,8 +76,8 @@ enum { LDD_DIR_AUTO = 0, LDD_DIR_TOP_DOWN = 1, LDD_DIR_BOTTOM_UP = 2 };
  * at once) running every round with a barrier in device memory per round or per few rounds (top-down only:
  * for large graphs of low degree and many rounds, such as grids).  AUTO: a graph of more than 7 arcs
  * per vertex on average, or a call with direction LDD_DIR_BOTTOM_UP, takes the launch engine; a
- * sparser graph takes one workgroup when it has at most 2^15 arcs, else a team, unless a vertex
- * has more than 4096 arcs (the team finds it in its preparation and the call continues on the
+ * sparser graph takes one workgroup when it has at most 2^15 arcs and 2^14 vertices, else a team, unless
+ * a vertex has more than 4096 arcs (the team finds it in its preparation and the call continues on the
  * launch engine).  ldd_tune may pick any of them. */
 enum {
   LDD_ENGINE_AUTO = 0,

@@ -642,15 +642,19 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
 // (RMAT and other skewed graphs, random graphs of small diameter) go to the multi-block engines,
 // whose bottom-up pulls and grid-wide arc splits they need.  Sparser graphs (meshes, geometric and
 // road-like graphs: many rounds with small frontiers) go to one workgroup when they have at most
-// BLOCK_AUTO_ARCS arcs (one workgroup reads them faster than round steps over the whole GPU
-// synchronise), else to a team, which refuses a graph with a vertex of more than AUTO_TEAM_DEG_CAP
-// arcs (one member would expand it alone), and that graph goes to the multi-block engines too.
+// BLOCK_AUTO_ARCS arcs and BLOCK_AUTO_VERTICES vertices (one workgroup reads them faster than round steps
+// over the whole GPU synchronise; but its preparation and output take 1.8 ns a vertex, against 55 us for a
+// team's on 262,144 vertices, so few arcs on many vertices, the late levels of a block decomposition, take
+// 0.12 ms on a team and 0.7 ms alone), else to a team, which refuses a graph with a vertex of more than
+// AUTO_TEAM_DEG_CAP arcs (one member would expand it alone), and that graph goes to the multi-block engines
+// too.
 // Measured (ms, launch engine -> team): rgg (6 arcs per vertex) 50K/200K/1M/4M vertices
 // 3.8/5.3/6.5/10.3 -> 1.6/2.3/2.6/4.5, grid2d-1000/3000 6.6/12.5 -> 2.7/5.3, grid3d-128 4.4 -> 1.8,
 // ER with 4 arcs per vertex, 2M vertices 0.69 -> 0.63; but ER with 8-10 arcs per vertex (small
 // diameter, huge frontiers, where the top-down team reads every arc) 4M/8M vertices 1.0/1.3 ->
 // 1.4/3.6 (50K/200K: 0.28/0.32 -> 0.16/0.20), and RMAT 10-20 0.18-0.30 -> 0.3-36.
 constexpr long long BLOCK_AUTO_ARCS = 1ll << 15;
+constexpr int BLOCK_AUTO_VERTICES = 1 << 14;
 constexpr long long AUTO_TEAM_DEGREE = 7;
 constexpr int AUTO_TEAM_DEG_CAP = 4096;
 
@@ -778,8 +782,9 @@ static ldd_status decompose_impl(Workspace& w, const ldd_csr* g, const int64_t* 
                                  const BatchView* bv) {
   // a forced bottom-up policy needs the multi-block engines (the workgroup engines run top-down)
   const bool sparse = g->nnz <= AUTO_TEAM_DEGREE * (long long)g->n && o.direction != LDD_DIR_BOTTOM_UP;
-  const bool auto_wg = o.engine == LDD_ENGINE_AUTO && sparse && g->nnz <= BLOCK_AUTO_ARCS;
-  const bool auto_team = o.engine == LDD_ENGINE_AUTO && sparse && g->nnz > BLOCK_AUTO_ARCS;
+  const bool small = g->nnz <= BLOCK_AUTO_ARCS && g->n <= BLOCK_AUTO_VERTICES;
+  const bool auto_wg = o.engine == LDD_ENGINE_AUTO && sparse && small;
+  const bool auto_team = o.engine == LDD_ENGINE_AUTO && sparse && !small;
   if (!bv && (o.engine == LDD_ENGINE_WORKGROUP || o.engine == LDD_ENGINE_TEAM || auto_wg || auto_team)) {
     const bool team = o.engine == LDD_ENGINE_TEAM || auto_team;
     ldd_status s = decompose_block(w, g, shift_fix, centre, cut_edges, o, stats, st, team,
