@@ -99,7 +99,7 @@ typedef struct {
   int32_t tail_vertices;  /* finish by label correction once unsettled vertices * this <= active vertices
                              (0 = default 32, -1 = never)                                                      */
   int32_t batch_mode;     /* ldd_decompose_batch: LDD_BATCH_* (below)                                    */
-  int32_t team_arcs;      /* workgroup batch engine: arcs per workgroup of a team (0 = default: all arcs over
+  int32_t team_arcs;      /* workgroup batch engine: arcs per workgroup of a team (0 = default: 3/4 of all arcs over
                              the grid, at least 2^14; -1 = no teams: one workgroup per graph)                 */
   int32_t reserved[7];
 } ldd_options;

@@ -920,13 +920,15 @@ ldd_status ldd_batch_workgroup(int32_t G, const int64_t* vtx_off, const int64_t*
     // one workgroup per CU by default: on the 512-graph benchmark batch one per CU ran 17% faster
     // than two (6.35 vs 7.69 ms), the memory system being the shared resource
     int grid = o.blocks > 0 ? o.blocks : w.num_cu;
-    // Teams: a graph with more arcs than a workgroup's share of the batch (all arcs over the grid,
-    // at least 2^14; or team_arcs when given) runs on K = ceil(arcs / share) workgroups (at most
+    // Teams: a graph with more arcs than a workgroup's share of the batch (three quarters of all arcs over
+    // the grid, at least 2^14; or team_arcs when given) runs on K = ceil(arcs / share) workgroups (at most
     // TEAM_MAX, at most a quarter of the grid, at least 64 vertices per member), so that no graph
-    // holds one workgroup long after the others are done.
+    // holds one workgroup long after the others are done.  A team takes two to three times the
+    // workgroup time of a workgroup alone (its claims are global atomics), which is what the share
+    // balances: the 512-graph batch takes 4.4 / 4.3 / 4.5 / 4.9 ms at half / three quarters / one / one and a half.
     const long long M = arc_off[G];
     std::vector<int> team((size_t)G, 1);
-    const long long share = o.team_arcs > 0 ? o.team_arcs : std::max(M / grid, 1ll << 14);
+    const long long share = o.team_arcs > 0 ? o.team_arcs : std::max(M / 4 * 3 / grid, 1ll << 14);
     const int kcap = o.team_arcs < 0 ? 1 : std::min(TEAM_MAX, grid / 4);
     for (int g = 0; g < G; ++g) {
       const long long e = arc_off[g + 1] - arc_off[g], nv = vtx_off[g + 1] - vtx_off[g];
