@@ -510,22 +510,32 @@ __device__ __forceinline__ void walk_heavy(const BlockJob& j, BlockShared& sh, i
 // Offers applied to the labels in memory.  filter: a far end's label is loaded first and the atomic is left
 // out when it cannot drop; without it the chain is one access shorter, which pays while few rows
 // are in flight.  Every label that may have dropped goes to won(w, first arc of w, degree of w, old
-// label, offer); EAGER: w's row offsets are read while the atomic is in flight (else 0, 0).
-template <int SC, bool EAGER, class Won>
+// label, offer); EAGER: w's row offsets are read while the atomic is in flight (else 0, 0).  With filter an offer
+// is left out, too, when seen(w, offer) knows of one as good.
+struct SeenNone {
+  __device__ __forceinline__ bool operator()(int, u64) const { return false; }
+};
+template <int SC, bool EAGER, class Won, class Seen = SeenNone>
 struct Relax {
   const BlockJob& j;
   bool filter;
   const Won& won;
+  Seen seen = Seen{};
   template <int U>
   __device__ __forceinline__ void run(const int (&w)[U], const bool (&in)[U], const u64 (&offer)[U]) const {
     u64 pw[U], old[U];
     int b0[U], bd[U];
     bool go[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) pw[k] = filter && in[k] ? wg_load(&j.P[w[k]]) : INF;
+    for (int k = 0; k < U; ++k) {
+      go[k] = in[k];
+      if (filter && in[k]) go[k] = !seen(w[k], offer[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) pw[k] = filter && go[k] ? wg_load(&j.P[w[k]]) : INF;
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      go[k] = in[k] && pw[k] > offer[k];
+      go[k] = go[k] && pw[k] > offer[k];
       b0[k] = bd[k] = 0;
       if (go[k]) {
         old[k] = lab_min<SC>(&j.P[w[k]], offer[k]);
@@ -537,7 +547,7 @@ struct Relax {
       if (go[k]) won(w[k], b0[k], bd[k], old[k], offer[k]);
   }
 };
-constexpr unsigned FILTER_MIN = 128;  // frontiers of more rows load the label first
+constexpr unsigned FILTER_MIN = 64;  // frontiers of more rows load the label first
 
 // A frontier's entries in LDS: buffer b of v (vertex), a (first arc), d (degree), and l (label).
 template <int CAP>
@@ -1654,6 +1664,47 @@ __device__ __attribute__((noinline)) unsigned team_step1(BlockShared& sh, g_cint
   return team_step_end<false, true>(sh, n, nxt, gcnt, 0, sh.cnt3[0]);
 }
 
+// Rounds per step.  A step of one round costs the team a barrier and the queue's way through device memory
+// (about 6 us in all) beside its rounds' chains (about 3 us each); STEP_MAX rounds share them.  But a
+// member alone relaxes what it reached in the step, so the frontier must not grow fast (a random
+// graph's explosion would stay in few members and overflow their LDS, and reach most vertices by
+// detours) and must fit their LDS: the rounds double while the frontier grows by less than half a step
+// (plus STEP_SLACK entries) and a member's share stays below STEP_SHARE, and halve otherwise; shares of at
+// most STEP_SMALL rows take up to STEP_MAX_SMALL rounds (1000^2 grid: 1.84 ms with 8, 1.58 with 16; the 256^3
+// grid's larger shares drift apart in 16: 3.7 against 3.9 ms).
+// MIN_SHARE: a small frontier is left to fewer members, so that each has a connected patch of it (random
+// geometric graph of 150,001 vertices: 0.65 / 0.60 / 0.58 ms at 32 / 16 / 8 rows).
+constexpr int STEP_MAX = 8, STEP_MAX_SMALL = 16, STEP_BITS = 4;
+static_assert(STEP_MAX <= 1 << STEP_BITS && STEP_MAX_SMALL <= 1 << STEP_BITS, "");
+constexpr unsigned STEP_SMALL = 64;
+constexpr unsigned STEP_SLACK = 8;
+constexpr unsigned STEP_SHARE = 1024;
+constexpr unsigned MIN_SHARE = 8;
+
+// The offers a team member made in this step, one per slot in LDS: a patch of a mesh's frontier offers the
+// same label to a vertex from up to three sides, and each would load that label and send an atomic
+// (27 G/s over the GPU).  The vertex is known by its slot (its low bits, folded) and its high bits, which
+// lie above the offer's distance from the step's first label: 2 B + 12 bits for steps of up to 16 rounds.  A
+// slot keeps the smallest entry; an offer that finds its own vertex with one as good is left out (256^3 grid:
+// 4.1 -> 3.7 ms, 32.5 million atomics for 16.8 million labels).
+constexpr int SEEN = 4096;  // slots, beside the queues
+static_assert(TEAM_Q_BYTES + 8 * SEEN <= BLOCK_LDS_BYTES, "");
+struct SeenOffers {
+  u64 base;
+  int bits;  // of an offer's distance from base; 0: not kept (labels too wide, or of any round)
+  __device__ static u64& at(unsigned i) { return reinterpret_cast<u64*>(blk_dyn + TEAM_Q_BYTES)[i]; }
+  __device__ static void clear() {
+    for (int i = threadIdx.x; i < SEEN; i += BT) at((unsigned)i) = INF;
+  }
+  __device__ __forceinline__ bool operator()(int w, u64 offer) const {
+    const u64 off = offer - base;
+    if (!bits || off >> bits) return false;  // (an entry left over from an earlier step may offer less than base)
+    const u64 mine = (u64)((unsigned)w >> 12) << bits | off;
+    const u64 old = atomicMin(&at(((unsigned)w ^ (unsigned)w >> 12) & (SEEN - 1)), mine);
+    return old <= mine && old >> bits == mine >> bits;
+  }
+};
+
 // A step of several rounds r, r + 1, ... (or tail sweeps): the first relaxes the member's share [e0, e1)
 // of the shared frontier, each later one what the member itself lowered in the round before (entries
 // in LDS, with the label they were given); each wakes the member's own bucket of that round.  What the last
@@ -1680,6 +1731,8 @@ __device__ __attribute__((noinline)) unsigned team_steps(BlockShared& sh, g_cint
   g_u64* gcnt = &sh.ts->qcnt[sh.epoch % 3];
   unsigned firsts = 0, ex = 0;
   int ci = 0;
+  const SeenOffers seen{(u64)r << (FIX + B), !SWEEP && 2 * B + 12 <= 64 ? FIX + B + STEP_BITS : 0};
+  bool filled = false;  // (cleared when the first round that filters begins)
 #pragma unroll 1
   for (int k = 0; k < rounds; ++k) {
     const int ib = k & 1;  // the LDS buffer read; the other one is written
@@ -1693,7 +1746,12 @@ __device__ __attribute__((noinline)) unsigned team_steps(BlockShared& sh, g_cint
       firsts += old == INF;
       if (old > offer) app(w, a0, deg, offer);
     };
-    const Relax<AG, true, decltype(won)> relax{j, nin > FILTER_MIN, won};
+    if (!filled && nin > FILTER_MIN) {
+      SeenOffers::clear();
+      __syncthreads();
+      filled = true;
+    }
+    const Relax<AG, true, decltype(won), SeenOffers> relax{j, nin > FILTER_MIN, won, seen};
     if (!SWEEP && r + k <= D) {
       const int w1 = sh.woff[r + k + 1];
       for (int t = sh.woff[r + k] + (int)threadIdx.x; t < w1; t += BT) team_wake(j, j.wk + sh.tlo + t, mask, won);
@@ -1731,21 +1789,10 @@ __device__ __attribute__((noinline)) unsigned team_steps(BlockShared& sh, g_cint
   return team_step_end<false, false>(sh, n, nxt, gcnt, rounds & 1, sh.cnt3[ci]);
 }
 
-// Rounds per step.  A step of one round costs the team a barrier and the queue's way through device memory
-// (about 6 us in all) beside its rounds' chains (about 3 us each); STEP_MAX rounds share them.  But a
-// member alone relaxes what it reached in the step, so the frontier must not grow fast (a random
-// graph's explosion would stay in few members and overflow their LDS, and reach most vertices by
-// detours) and must fit their LDS: the rounds double while the frontier grows by less than half a step
-// (plus STEP_SLACK entries) and a member's share stays below STEP_SHARE, and halve otherwise.
-// MIN_SHARE: a small frontier is left to fewer members, so that each has a connected patch of it.
-constexpr int STEP_MAX = 8;
-constexpr unsigned STEP_SLACK = 8;
-constexpr unsigned STEP_SHARE = 512;
-constexpr unsigned MIN_SHARE = 32;
-
 __device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K) {
   if (spill || nf > STEP_SHARE * (unsigned)K) return 1;
-  if (nf <= before + before / 2 + STEP_SLACK) return rounds < STEP_MAX ? 2 * rounds : STEP_MAX;
+  const int most = nf > STEP_SMALL * (unsigned)K ? STEP_MAX : STEP_MAX_SMALL;
+  if (nf <= before + before / 2 + STEP_SLACK) return 2 * rounds < most ? 2 * rounds : most;
   return rounds > 1 ? rounds / 2 : 1;
 }
 
