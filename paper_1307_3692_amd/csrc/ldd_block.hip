@@ -1224,6 +1224,111 @@ __device__ void block_graph(BlockShared& sh, BlockOut* out) {
 // centre, plus one block of passes (fewer, since labels lowered early in a pass are read later in
 // the same pass).
 // Labels are 8-byte LDS words written whole, so a concurrent read sees the old or the new label.
+//
+// What bounds a pass is its LDS accesses and instructions.  A thread keeps its first FIX_V vertices' labels
+// (it alone writes them) and the first RD columns of each, as 16-bit ids, in registers, so that an arc
+// costs one LDS read and a 64-bit minimum; a missing arc reads the vertex itself, whose offer is
+// never lower.  With row offsets and columns read from LDS in every pass (the columns of 64 rows of four
+// in conflicting banks) a pass of the 64 x 64 grid took 2.2 us, so 0.9: its 20 label accesses per thread are
+// 0.55 us of the LDS's 128 bytes a cycle.  A decomposition of that grid at beta 0.1 (40 passes) went from 113 to
+// 61 us, 46 of them this kernel.  Two or eight passes between barriers measure the same within 2 us.
+constexpr int FIX_V = 6;
+constexpr int FIX_BLOCK = 4;  // passes between two barriers
+
+struct FixGraph {
+  u64* P;           // LDS: labels
+  const int* rp;    // LDS: row offsets, columns
+  const int* col;
+  int n, degmax, B;
+  u64 unit;
+};
+
+// The passes and the output.  Passes run FIX_BLOCK at a time with no barrier between them (in-place
+// relaxation is exact in any interleaving); a block of passes in which no thread lowered any label
+// read only final labels, so the labels are the fixpoint.
+template <int RD>
+__device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u64* labels, long long* passes_out,
+                                           bool* converged_out, u64* cut2, u64* pieces) {
+  const int n = g.n, tid = threadIdx.x;
+  u64* P = g.P;
+  const int* __restrict__ rp = g.rp;   // the CSR in LDS is never written during the passes
+  const int* __restrict__ col = g.col;
+  const bool rest = g.degmax > RD;
+  unsigned id[FIX_V][RD / 2];
+  u64 p[FIX_V];
+#pragma unroll
+  for (int k = 0; k < FIX_V; ++k) {
+    const int v = tid + k * BT, a0 = v < n ? rp[v] : 0, a1 = v < n ? rp[v + 1] : 0;
+    p[k] = v < n ? P[v] : 0;
+#pragma unroll
+    for (int e = 0; e < RD / 2; ++e) {
+      const int x = a0 + 2 * e < a1 ? col[a0 + 2 * e] : v, y = a0 + 2 * e + 1 < a1 ? col[a0 + 2 * e + 1] : v;
+      id[k][e] = (unsigned)x | (unsigned)y << 16;
+    }
+  }
+  long long passes = 0;
+  bool converged = false;
+  for (;;) {
+    int changed = 0;
+    for (int i = 0; i < FIX_BLOCK; ++i) {
+#pragma unroll
+      for (int k = 0; k < FIX_V; ++k) {
+        const int v = tid + k * BT;
+        if (v < n) {
+          u64 best = INF;
+#pragma unroll
+          for (int e = 0; e < RD / 2; ++e) {
+            const u64 q = P[id[k][e] & 0xffff], t = P[id[k][e] >> 16];
+            const u64 m = q < t ? q : t;
+            best = m < best ? m : best;
+          }
+          if (rest) {
+            const int a1 = rp[v + 1];
+            for (int a = rp[v] + RD; a < a1; ++a) {
+              const u64 q = P[col[a]];
+              best = q < best ? q : best;
+            }
+          }
+          best += g.unit;
+          if (best < p[k]) {
+            P[v] = p[k] = best;
+            changed = 1;
+          }
+        }
+      }
+      for (int v = tid + FIX_V * BT; v < n; v += BT) {
+        const int a1 = rp[v + 1];
+        const u64 own = P[v];
+        u64 best = own;
+        for (int a = rp[v]; a < a1; ++a) {
+          const u64 q = P[col[a]] + g.unit;
+          best = q < best ? q : best;
+        }
+        if (best < own) {
+          P[v] = best;
+          changed = 1;
+        }
+      }
+    }
+    passes += FIX_BLOCK;
+    converged = !__syncthreads_or(changed);
+    if (converged || passes > (long long)n + 1 + FIX_BLOCK) break;
+  }
+  // centres, pieces, cut; the labels to the graph's label array
+  const u64 mask = ((u64)1 << g.B) - 1;
+  for (int v = tid; v < n; v += BT) {
+    const u64 q = P[v];
+    const int c = (int)(q & mask);
+    centre[v] = c;
+    labels[v] = q;
+    *pieces += c == v;
+    const int a1 = rp[v + 1];
+    for (int a = rp[v]; a < a1; ++a) *cut2 += (int)(P[col[a]] & mask) != c;
+  }
+  *passes_out = passes;
+  *converged_out = converged;
+}
+
 __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, BlockOut* out) {
   const BlockJob j = job_of(sh);
   const int n = j.n;
@@ -1238,27 +1343,51 @@ __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, Block
   if (tid == 0) sh.err = 0;
   __syncthreads();
   unsigned err = 0;
-  u64 dmax = 0, active = 0;
+  u64 dmax = 0;
   if (tid == 0 && n > 0 && (rp[0] != 0 || (long long)rp[n] != nnz)) err |= ERR_BAD_ROWPTR;
-  for (int v = tid; v <= n; v += BT) {
-    const int a0 = rp[v];
-    lrp[v] = a0;
-    if (v == n) break;
-    const int a1 = rp[v + 1];
-    const long long s = shift[v];
-    if (s < 0 || s > (1ll << 52)) err |= ERR_BAD_SHIFT;
-    if (a1 < a0) err |= ERR_BAD_ROWPTR;
-    active += a1 > a0;
-    dmax = (u64)s > dmax ? (u64)s : dmax;
+  u64 active = 0, degmax = 0;
+  for (int v0 = tid; v0 < n; v0 += VU * BT) {
+    long long s[VU];
+    int a0[VU], deg[VU];
+#pragma unroll
+    for (int k = 0; k < VU; ++k) {
+      const int v = v0 + k * BT;
+      s[k] = 0;
+      a0[k] = deg[k] = 0;
+      if (v < n) {
+        s[k] = shift[v];
+        row_of(rp, v, &a0[k], &deg[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < VU; ++k) {
+      const int v = v0 + k * BT;
+      if (v < n) {
+        if (s[k] < 0 || s[k] > (1ll << 52)) err |= ERR_BAD_SHIFT;
+        if (deg[k] < 0) err |= ERR_BAD_ROWPTR;
+        lrp[v] = a0[k];
+        P[v] = (u64)s[k];  // the shift, until Delta is known
+        active += deg[k] > 0;
+        degmax = deg[k] > 0 && (u64)deg[k] > degmax ? (u64)deg[k] : degmax;
+        dmax = (u64)s[k] > dmax ? (u64)s[k] : dmax;
+      }
+    }
   }
-  for (long long a = tid; a < nnz; a += BT) {
-    const int c = col[a];
-    if ((unsigned)c >= (unsigned)n) err |= ERR_BAD_COL;
-    lcol[a] = c;
+  if (tid == 0) lrp[n] = (int)nnz;
+  for (long long a0 = tid; a0 < nnz; a0 += VU * BT) {
+    int c[VU];
+#pragma unroll
+    for (int k = 0; k < VU; ++k) c[k] = a0 + k * BT < nnz ? col[a0 + k * BT] : 0;
+#pragma unroll
+    for (int k = 0; k < VU; ++k) {
+      if ((unsigned)c[k] >= (unsigned)n) err |= ERR_BAD_COL;
+      if (a0 + k * BT < nnz) lcol[a0 + k * BT] = c[k];
+    }
   }
   if (err) atomicOr(&sh.err, err);
   const u64 delta = block_max64(dmax, sh);
   const u64 n_active = block_sum64(active, sh);
+  degmax = block_max64(degmax, sh);
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   __syncthreads();
   if (tid == 0) {
@@ -1274,50 +1403,14 @@ __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, Block
     }
     return;
   }
-  for (int v = tid; v < n; v += BT) P[v] = ((delta - (u64)shift[v]) << B) | (u64)v;
+  for (int v = tid; v < n; v += BT) P[v] = ((delta - P[v]) << B) | (u64)v;
   __syncthreads();
-  const u64 unit = (u64)1 << (FIX + B);
-  // Passes run FIX_BLOCK at a time with no barrier between them (in-place relaxation is exact in
-  // any interleaving); a block of passes in which no thread lowered any label read only final
-  // labels, so the labels are the fixpoint.
-  constexpr int FIX_BLOCK = 4;
+  const FixGraph g{P, lrp, lcol, n, (int)degmax, B, (u64)1 << (FIX + B)};
   long long passes = 0;
   bool converged = false;
-  const int* __restrict__ rrp = lrp;   // the CSR in LDS is never written during the passes
-  const int* __restrict__ rcol = lcol;
-  for (;;) {
-    int changed = 0;
-    for (int k = 0; k < FIX_BLOCK; ++k) {
-      for (int v = tid; v < n; v += BT) {
-        const int a0 = rrp[v], a1 = rrp[v + 1];
-        const u64 p = P[v];
-        u64 best = p;
-        for (int a = a0; a < a1; ++a) {
-          const u64 q = P[rcol[a]] + unit;
-          best = q < best ? q : best;
-        }
-        if (best < p) {
-          P[v] = best;
-          changed = 1;
-        }
-      }
-    }
-    passes += FIX_BLOCK;
-    converged = !__syncthreads_or(changed);
-    if (converged || passes > (long long)n + 1 + FIX_BLOCK) break;
-  }
-  // centres, pieces, cut; the labels to the graph's label array
-  const u64 mask = ((u64)1 << B) - 1;
   u64 cut2 = 0, pieces = 0;
-  for (int v = tid; v < n; v += BT) {
-    const u64 p = P[v];
-    const int c = (int)(p & mask);
-    j.centre[v] = c;
-    j.P[v] = p;
-    pieces += c == v;
-    const int a1 = lrp[v + 1];
-    for (int a = lrp[v]; a < a1; ++a) cut2 += (int)(P[lcol[a]] & mask) != c;
-  }
+  if (degmax <= 4) fix_passes<4>(g, j.centre, j.P, &passes, &converged, &cut2, &pieces);
+  else fix_passes<8>(g, j.centre, j.P, &passes, &converged, &cut2, &pieces);
   cut2 = block_sum64(cut2, sh);
   pieces = block_sum64(pieces, sh);
   if (tid == 0) {

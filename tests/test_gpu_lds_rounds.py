@@ -89,3 +89,17 @@ def test_frontier_explodes_inside_a_step(ldd, tail):
     s[n + length - 1] = 260 * S  # the path's far end starts the search
     check(ldd, rp, ci, s, dict(engine=4, tail_vertices=tail), dict(engine=4, blocks=5, tail_vertices=tail),
           dict(engine=4, blocks=40, tail_vertices=tail), dict(engine=3, tail_vertices=tail))
+
+
+# one graph held whole in LDS: four arcs of a vertex are in registers, eight, or eight and the rest read
+# from LDS; six vertices of a thread are, further ones are not; and one size past the LDS
+@pytest.mark.parametrize("degree", [4, 5, 8, 9, 300])
+@pytest.mark.parametrize("n", [301, 1023, 1025, 6144, 6145, 7300])
+def test_graph_in_lds(ldd, n, degree):
+    """A ring with one vertex of the given degree and a few of four."""
+    src = np.arange(n)
+    es, ed = [src, np.arange(0, n - n % 7, 7)], [(src + 1) % n, (np.arange(0, n - n % 7, 7) + n // 2) % n]
+    es.append(np.full(degree - 2, 5))
+    ed.append(5 + 2 * np.arange(1, degree - 1) % n)
+    rp, ci = inputs.from_edges(n, np.concatenate(es), np.concatenate(ed) % n)
+    check(ldd, rp, ci, inputs.make_shifts(n, 0.02, n + degree), dict(engine=3), dict(engine=3, tail_vertices=-1))
