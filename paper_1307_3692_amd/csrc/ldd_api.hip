@@ -108,6 +108,10 @@ struct Workspace {
   void* stamp_clean = nullptr;  // ... while this equals stamp.p
   Buf hist, cursor, wake_off, next_ne, mat, qmax;        // per round / q-bucket (mat: per bucket and prep block)
   Buf cand, cand_cnt;                                    // per prep block: first-window candidates
+  // control blocks: two that single decompositions take in turn (each clears the other for the next
+  // call; ctrl_clean: that has been done in ctrl.p for ctrl_next), and the batch's
+  int ctrl_next = 0;
+  void* ctrl_clean = nullptr;
   Buf ctrl, st, qcnt, lr_part, lb, ex_part, vr;
   // workgroup engine: queues and wake order (3 ints per vertex), jobs, order, results, job counter
   Buf bk_wq, bk_jobs, bk_order, bk_out, bk_cnt, bk_team, bk_sync;
@@ -158,7 +162,7 @@ ldd_status ws_setup(Workspace& w) {
     w.block_coresident = w.num_cu * std::max(per_cu_block, 1);
   }
   ldd_status s;
-  if ((s = grow(w.ctrl, sizeof(Ctrl))) || (s = grow(w.st, 2 * sizeof(RoundState))) ||
+  if ((s = grow(w.ctrl, 3 * sizeof(Ctrl))) || (s = grow(w.st, 2 * sizeof(RoundState))) ||
       (s = grow(w.qcnt, 3 * 16 * sizeof(u64))) || (s = grow(w.lr_part, 2 * (size_t)RT * sizeof(u64))) ||
       (s = grow(w.lb, sizeof(LaunchBlock))) || (s = grow(w.ex_part, (size_t)RT * sizeof(u64))))
     return s;
@@ -232,6 +236,7 @@ extern "C" void ldd_release_workspace(void) {
     b->p = nullptr;
     b->bytes = 0;
   }
+  w->stamp_clean = w->ctrl_clean = nullptr;  // new memory may come to lie at the same address
 }
 
 // ------------------------------------------------------------------------------------------
@@ -321,7 +326,7 @@ static ldd_status max_radius(Workspace& w, int n, const int64_t* shift_fix, u64 
 }
 
 // One decomposition.  wide = false: the sorted (q-bucket) layout, enqueued in full without the
-// host waiting (k_setup decides on the device whether the rounds run); if the shifts turn out to
+// host waiting (k_plan decides on the device whether the rounds run); if the shifts turn out to
 // span QCAP units or more, the run reports REDO_WIDE and is redone with wide = true, whose
 // preparation reads Delta on the host to size its per-round arrays.
 static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* shift_fix, int32_t* centre,
@@ -336,21 +341,23 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
       (s = grow(w.qa1, nv * 4)) || (s = grow(w.wake_ord, nv * 4)) || (s = grow(w.stamp, nv * 4)) ||
       (s = grow(w.hub_bits, (nv + 63) / 64 * 8)))
     return s;
-  Ctrl* ctrl = (Ctrl*)w.ctrl.p;
+  Ctrl* const ctrl = (Ctrl*)w.ctrl.p + w.ctrl_next;
   u64* P = (u64*)w.P.p;
   const int B = ceil_log2(n) < 1 ? 1 : ceil_log2(n);
 
   // the previous call on this workspace may have left idle steps queued on its stream, which
   // read the argument block and the state this call is about to rewrite: start after them
   HIP_TRY(hipStreamWaitEvent(st, w.ev[2], 0));
-  HIP_TRY(hipEventRecord(w.ev[0], st));
+  // events between kernels only where their times are asked for: each holds the next kernel back
+  if (stats) HIP_TRY(hipEventRecord(w.ev[0], st));
   const int g_n = grid_for(n, 256 * 4, 2048);
   // preparation pass A: labels, Delta, checks and the q-bucket histogram (per block)
   const int gp = (int)std::min<long long>(1024, std::max<long long>(1, n / 16384));
   if ((s = grow(w.mat, (size_t)QCAP * gp * 4)) || (s = grow(w.qmax, (size_t)gp * 4)) ||
       (s = grow(w.cand, (size_t)CAND * gp * 8)) || (s = grow(w.cand_cnt, (size_t)gp * 4)))
     return s;
-  HIP_TRY(hipMemsetAsync(ctrl, 0, sizeof(Ctrl), st));
+  if (w.ctrl_clean != w.ctrl.p) HIP_TRY(hipMemsetAsync(ctrl, 0, sizeof(Ctrl), st));
+  w.ctrl_clean = nullptr;  // until this call has cleared the other one
   hipLaunchKernelGGL(k_init, dim3(gp), dim3(1024), 0, st, n, nnz, g->row_ptr, (const long long*)shift_fix, P, ctrl,
                      (unsigned*)w.mat.p, (int*)w.qmax.p, (u64*)w.cand.p, (unsigned*)w.cand_cnt.p);
   if (o.validate && nnz > 0)
@@ -364,13 +371,9 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
     const size_t nq = (size_t)QCAP + 2;
     if ((s = grow(w.hist, nq * 4)) || (s = grow(w.wake_off, nq * 4)) || (s = grow(w.next_ne, nq * 4))) return s;
     R_bound = QCAP;
-    hipLaunchKernelGGL(k_qbucket_scan, dim3(std::min(QCAP, 1024)), dim3(256), 0, st, gp, (unsigned*)w.mat.p,
-                       (const int*)w.qmax.p, (unsigned*)w.hist.p, (const Ctrl*)ctrl);
-    hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), 0, st, (const Ctrl*)ctrl, (const unsigned*)w.hist.p,
-                       (int*)w.wake_off.p, (int*)w.next_ne.p);
-    hipLaunchKernelGGL(k_place_window, dim3(gp), dim3(256), 0, st, (const Ctrl*)ctrl, (const unsigned*)w.mat.p,
-                       (const int*)w.qmax.p, (const int*)w.wake_off.p, (const u64*)w.cand.p,
-                       (const unsigned*)w.cand_cnt.p, (int*)w.wake_ord.p);
+    if (gp > PLAN_BLOCKS)
+      hipLaunchKernelGGL(k_qbucket_scan, dim3(std::min(QCAP, 1024)), dim3(256), 0, st, gp, (unsigned*)w.mat.p,
+                         (const int*)w.qmax.p, (unsigned*)w.hist.p, (const Ctrl*)ctrl);
   } else {
     // shifts spanning QCAP units or more: exact wake rounds via global atomics, arrays sized
     // by the rounds bound the host reads first
@@ -415,7 +418,7 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
   const unsigned stamp_base = w.stamp_base;
   w.stamp_clean = nullptr;  // unknown until this call's steps are counted
 
-  // round arguments; Delta, the rounds bound and the vertices with arcs are filled in by k_setup
+  // round arguments; Delta, the rounds bound and the vertices with arcs are filled in by k_plan
   RoundCtx c{};
   c.n = n;
   c.B = B;
@@ -456,7 +459,9 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
   rep->tail_hint = 0;
 
   const int engine = o.engine == LDD_ENGINE_PERSISTENT ? LDD_ENGINE_PERSISTENT : LDD_ENGINE_LAUNCH;
-  int blocks = o.blocks > 0 ? o.blocks : 2 * w.num_cu;
+  // two blocks per CU, but fewer on small graphs, whose steps dispatch in less time (R-MAT 12: 170 -> 160 us,
+  // R-MAT 16: 250 -> 235 us with 128 and 256 blocks; R-MAT 20 has all)
+  int blocks = o.blocks > 0 ? o.blocks : std::min(2 * w.num_cu, std::max(128, n / 256));
   if (blocks > RT) blocks = RT;  // the per-block minima of a step are reduced by one block
   if (engine == LDD_ENGINE_PERSISTENT && blocks > w.max_coresident) blocks = w.max_coresident;
   // rounds, placement steps, tail sweeps (each settles or lowers at least one label) and slack
@@ -466,9 +471,18 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
   if (engine != LDD_ENGINE_PERSISTENT)
     for (int i = 0; i < 3; ++i)
       if ((s = step_graph(w, blocks, CHUNK_SIZES[i], &exec[i]))) return s;
-  hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, c, (LaunchBlock*)w.lb.p, wide ? 0 : 1);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, st, c, (LaunchBlock*)w.lb.p, wide ? 0 : 1,
+                     gp <= PLAN_BLOCKS ? 1 : 0, (unsigned*)w.mat.p, (const unsigned*)w.hist.p, (const u64*)w.cand.p,
+                     (const unsigned*)w.cand_cnt.p, (int*)w.wake_off.p, (int*)w.next_ne.p,
+                     (Ctrl*)w.ctrl.p + (w.ctrl_next ^ 1));
+  if (!wide && gp > PLAN_BLOCKS)
+    hipLaunchKernelGGL(k_place_window, dim3(gp), dim3(256), 0, st, (const Ctrl*)ctrl, (const unsigned*)w.mat.p,
+                       (const int*)w.qmax.p, (const int*)w.wake_off.p, (const u64*)w.cand.p,
+                       (const unsigned*)w.cand_cnt.p, (int*)w.wake_ord.p);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipEventRecord(w.ev[1], st));
+  w.ctrl_next ^= 1;
+  w.ctrl_clean = w.ctrl.p;
+  if (stats) HIP_TRY(hipEventRecord(w.ev[1], st));
   // The host spins on the report (written by the step that finds the rounds done) and on the
   // oldest replay's completion, which makes room for another.  Replays still queued after the
   // report return at once; the output pass runs on its own stream beside them.
@@ -556,16 +570,16 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
   }
   // output pass: every label is final once the report is there
   const hipStream_t so = w.out;
-  HIP_TRY(hipEventRecord(w.ev[3], so));
+  if (stats) HIP_TRY(hipEventRecord(w.ev[3], so));
   const int g_f = grid_for((n + 63) / 64, 128, 2048);  // whole bitmap words per block
   hipLaunchKernelGGL(k_finalize, dim3(g_f), dim3(512), 0, so, n, B, g->row_ptr, (const u64*)P, centre,
                      (u64*)w.hub_bits.p, (int*)w.qv0.p, (unsigned*)w.qa0.p, ctrl);
-  HIP_TRY(hipEventRecord(w.ev[4], so));
+  if (stats) HIP_TRY(hipEventRecord(w.ev[4], so));
   if (nnz > 0)
     hipLaunchKernelGGL(k_cut, dim3(grid_for(nnz, 256 * 8, 2048)), dim3(256), 0, so, n, g->row_ptr, g->col_idx,
                        (const int*)centre, (const u64*)w.hub_bits.p, (const int*)w.qv0.p, (const unsigned*)w.qa0.p,
                        ctrl, bv ? bv->gid : nullptr, bv ? bv->cut_g : nullptr);
-  HIP_TRY(hipEventRecord(w.ev[5], so));
+  if (stats) HIP_TRY(hipEventRecord(w.ev[5], so));
   hipLaunchKernelGGL(k_out_report, dim3(1), dim3(64), 0, so, (const Ctrl*)ctrl, c.report);
   HIP_TRY(hipGetLastError());
   if (stats) HIP_TRY(hipMemcpyAsync(w.host->ex_part, w.ex_part.p, (size_t)blocks * sizeof(u64), hipMemcpyDeviceToHost, so));
@@ -1059,8 +1073,8 @@ ldd_status ldd_batch_union(int32_t G, const int64_t* vtx_off, const int64_t* arc
   HIP_TRY(hipMemcpyAsync(d_ao, arc_off, (size_t)(G + 1) * 8, hipMemcpyHostToDevice, st));
   HIP_TRY(hipMemsetAsync(w.b_dg.p, 0, (size_t)(G + 1) * 128, st));
   HIP_TRY(hipMemsetAsync(w.b_cut.p, 0, (size_t)G * 8, st));
-  HIP_TRY(hipMemsetAsync(w.ctrl.p, 0, sizeof(Ctrl), st));
-  Ctrl* ctrl = (Ctrl*)w.ctrl.p;
+  Ctrl* ctrl = (Ctrl*)w.ctrl.p + 2;
+  HIP_TRY(hipMemsetAsync(ctrl, 0, sizeof(Ctrl), st));
   hipLaunchKernelGGL(k_batch_rows, dim3(grid_for(N, 256 * 4, 4096)), dim3(256), 0, st, G, (long long)N, d_vo, d_ao,
                      row_ptr, (const long long*)shift_fix, (int*)w.b_rp.p, (int*)w.b_gid.p, d_dg, ctrl);
   if (M > 0)

@@ -26,7 +26,7 @@ __device__ constexpr long long fix_lds_bytes(long long n, long long nnz) { retur
 // error bits of a workgroup job beyond ERR_*: the labels would not fit 64 bits; the shift range
 // needs more wake buckets than the workgroup sorts; a team was asked to refuse a graph with a
 // vertex of more than deg_cap arcs, and it has one; a team's queue had more entries than vertices
-// (repeated ones: see team_step).  The last three leave the graph to the multi-block engine.
+// (repeated ones: see team_steps).  The last three leave the graph to the multi-block engine.
 enum : unsigned { BLK_OVERFLOW = 64u, BLK_WIDE = 128u, BLK_SKEW = 256u, BLK_QUEUE = 512u };
 
 // A graph too large for one workgroup runs on a team of K workgroups (all resident at once) that

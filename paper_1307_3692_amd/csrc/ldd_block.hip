@@ -26,7 +26,7 @@
 // (its preparation, wake buckets, tail seed and output) and a share of every frontier, which is one
 // queue in device memory.  The members meet at a barrier in device memory, where the queue's length
 // and the error bits are read, once per step; a step is one round when the frontier is large or
-// grows fast, else several (see team_step).  The labels are then shared by several CUs, so their
+// grows fast, else several (see team_steps).  The labels are then shared by several CUs, so their
 // loads and atomics take device scope.
 #include "ldd_block.h"
 

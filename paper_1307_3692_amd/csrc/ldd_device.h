@@ -59,7 +59,7 @@ struct Ctrl {
   alignas(128) unsigned err;  // ERR_* bits
   unsigned wide;              // some shift has an integer part >= QCAP
   alignas(128) unsigned place_lo;  // lowest q-bucket every preparation block listed in full
-  unsigned setup;                  // SETUP_*: what k_setup found (the rounds run only on SETUP_OK)
+  unsigned setup;                  // SETUP_*: what k_plan found (the rounds run only on SETUP_OK)
   alignas(128) u64 bar;     // grid barrier arrival counter (persistent engine)
   alignas(128) u64 cut_arcs;  // 2 per arc to H plus 1 per two-sided cut arc outside H
   alignas(128) u64 pieces;  // vertices that are their own centre

@@ -12,6 +12,7 @@ enum { MODE_ROUNDS = 0, MODE_TAIL = 1, MODE_DONE = 2, MODE_PLACE = 3 };
 
 constexpr int RT = 1024;    // threads per block of the round kernels (16 waves)
 constexpr int ABUF = 4096;  // entries of a block's LDS append buffer
+constexpr int PLAN_BLOCKS = 16;  // preparation blocks up to which one workgroup plans and places the first window
 
 // State after round-kernel step k (k = 0 is the initial state written by the host).
 // All fields are 64-bit so that the state can be copied field by field with coherent
@@ -40,7 +41,7 @@ struct RoundState {
 };
 
 // What the host reads at the end, in mapped host memory.  The step that finds the rounds done
-// (or k_setup, when the rounds are not to run) writes the first part and then `ready`; the
+// (or k_plan, when the rounds are not to run) writes the first part and then `ready`; the
 // output pass writes the totals and then `out_ready`.
 struct Report {
   RoundState st;
@@ -143,7 +144,6 @@ struct LaunchBlock {
 __global__ void k_init(int n, long long nnz, const int* row_ptr, const long long* shift, u64* P, Ctrl* ctrl,
                        unsigned* mat, int* qmax, u64* cand, unsigned* cand_cnt);
 __global__ void k_qbucket_scan(int G, unsigned* mat, const int* qmax, unsigned* tot, const Ctrl* ctrl);
-__global__ void k_qscan(const Ctrl* ctrl, const unsigned* tot, int* qoff, int* next_ne);
 __global__ void k_place_window(const Ctrl* ctrl, const unsigned* mat, const int* qmax, const int* qoff, const u64* cand,
                                const unsigned* cand_cnt, int* wake_ord);
 __global__ void k_check_cols(int n, long long nnz, const int* col, Ctrl* ctrl);
@@ -157,7 +157,8 @@ __global__ void k_round_step_lb(const LaunchBlock* lb, int j);
 __global__ void k_round_step_srv(const LaunchBlock* lb, int j);
 __global__ void k_advance(LaunchBlock* lb, int C);
 __global__ void k_rounds_persistent(const LaunchBlock* lb);
-__global__ void k_setup(RoundCtx c, LaunchBlock* lb, int qpath);
+__global__ void k_plan(RoundCtx c, LaunchBlock* lb, int qpath, int fused, unsigned* mat, const unsigned* tot,
+                       const u64* cand, const unsigned* cand_cnt, int* qoff, int* next_ne, Ctrl* next);
 __global__ void k_out_report(const Ctrl* ctrl, Report* report);
 __global__ void k_max_radius(int n, int B, const u64* P, const long long* shift, u64 delta, u64* out);
 __global__ void k_finalize(int n, int B, const int* row_ptr, const u64* P, int* centre, u64* hub_bits, int* lv,

@@ -5,9 +5,10 @@
 //   k_init          labels := INF, Delta := max shift (Algorithm 1 step 2), CSR bounds checks,
 //                   per-block histogram of q = shift >> 20 and lists of the highest buckets
 //   k_qbucket_scan  per bucket, offsets of the blocks' counts
-//   k_qscan         bucket offsets and "next round that wakes anyone" links
+//   k_plan          bucket offsets and "next round that wakes anyone" links; initial round state
 //   k_place_window  the first window of buckets into the wake order (the round steps place
-//                   lower buckets if the rounds reach them)
+//                   lower buckets if the rounds reach them); k_plan does this and the bucket scan
+//                   when the preparation has few blocks
 //   (shifts spanning QCAP units or more: k_wake_count / k_wake_scan / k_wake_scatter, a
 //   counting sort by exact wake round w(u) = (Delta - shift_fix[u]) >> 20)
 //   rounds          one step per round (ldd_rounds.hip): wake the round's vertices, expand
@@ -225,16 +226,41 @@ __global__ __launch_bounds__(256) void k_qbucket_scan(int G, unsigned* __restric
   }
 }
 
-// One block: bucket offsets qoff[0..D+1] and, per round r (R = D + 1 rounds), the next round
+// Places the first wake window, buckets [q_lo, D] (q_lo = place_lo), from the blocks'
+// candidate lists (more than PLAN_BLOCKS of them).  A vertex's slot is its bucket's offset, plus the counts of the same bucket
+// in earlier preparation blocks, plus its rank inside its own block (an LDS cursor per bucket).
+__global__ __launch_bounds__(256) void k_place_window(const Ctrl* __restrict__ ctrl, const unsigned* __restrict__ mat,
+                                                      const int* __restrict__ qmax, const int* __restrict__ qoff,
+                                                      const u64* __restrict__ cand,
+                                                      const unsigned* __restrict__ cand_cnt,
+                                                      int* __restrict__ wake_ord) {
+  __shared__ unsigned cur[QCAP];
+  if (!qpath_ok(ctrl)) return;
+  const int D = (int)(ctrl->delta >> FIX);
+  const int q_lo = (int)ctrl->place_lo;
+  if (q_lo > D) return;
+  const unsigned G = gridDim.x;
+  const int qm = min(qmax[blockIdx.x], D);
+  for (int q = q_lo + (int)threadIdx.x; q <= qm; q += blockDim.x)
+    cur[q - q_lo] = (unsigned)qoff[q] + mat[(size_t)q * G + blockIdx.x];
+  __syncthreads();
+  const unsigned cnt = cand_cnt[blockIdx.x];
+  for (unsigned i = threadIdx.x; i < cnt; i += blockDim.x) {
+    const u64 e = cand[(size_t)blockIdx.x * CAND + i];
+    const int q = (int)(e >> 32);
+    if (q >= q_lo && q <= qm) wake_ord[atomicAdd(&cur[q - q_lo], 1u)] = (int)(unsigned)e;
+  }
+}
+
+// The block's bucket offsets qoff[0..D+1] and, per round r (R = D + 1 rounds), the next round
 // at or after r whose two q-buckets (D - r and D - r - 1) are not both empty.  Thread t takes
 // a run of consecutive buckets (rounds); the runs' sums are combined by an exclusive prefix
 // scan, their first non-empty rounds by a suffix minimum (wave shuffles, then across waves).
-__global__ __launch_bounds__(1024) void k_qscan(const Ctrl* __restrict__ ctrl, const unsigned* __restrict__ tot,
-                                                int* __restrict__ qoff, int* __restrict__ next_ne) {
+// tot: the buckets' totals (LDS); cur: the offsets again (LDS).
+__device__ __forceinline__ void qscan(int D, const unsigned* tot, unsigned* cur, int* __restrict__ qoff,
+                                      int* __restrict__ next_ne) {
   __shared__ unsigned w_sum[16];
   __shared__ int w_first[16];
-  if (!qpath_ok(ctrl)) return;
-  const int D = (int)(ctrl->delta >> FIX);
   const int Qn = D + 1, R = D + 1;
   const int t = threadIdx.x;
   const unsigned lane = lane_id(), wid = t / WAVE;
@@ -267,6 +293,7 @@ __global__ __launch_bounds__(1024) void k_qscan(const Ctrl* __restrict__ ctrl, c
   unsigned acc = before + incl - s;
   for (int i = lo; i < hi; ++i) {
     qoff[i] = (int)acc;
+    cur[i] = acc;
     acc += tot[i];
   }
   int nx = after;
@@ -280,42 +307,61 @@ __global__ __launch_bounds__(1024) void k_qscan(const Ctrl* __restrict__ ctrl, c
   }
 }
 
-// Places the first wake window, buckets [q_lo, D] (q_lo = place_lo), from the blocks'
-// candidate lists.  A vertex's slot is its bucket's offset, plus the counts of the same bucket
-// in earlier preparation blocks, plus its rank inside its own block (an LDS cursor per bucket).
-__global__ __launch_bounds__(256) void k_place_window(const Ctrl* __restrict__ ctrl, const unsigned* __restrict__ mat,
-                                                      const int* __restrict__ qmax, const int* __restrict__ qoff,
-                                                      const u64* __restrict__ cand,
-                                                      const unsigned* __restrict__ cand_cnt,
-                                                      int* __restrict__ wake_ord) {
-  __shared__ unsigned cur[QCAP];
-  if (!qpath_ok(ctrl)) return;
-  const int D = (int)(ctrl->delta >> FIX);
-  const int q_lo = (int)ctrl->place_lo;
-  if (q_lo > D) return;
-  const unsigned G = gridDim.x;
-  const int qm = min(qmax[blockIdx.x], D);
-  for (int q = q_lo + (int)threadIdx.x; q <= qm; q += blockDim.x)
-    cur[q - q_lo] = (unsigned)qoff[q] + mat[(size_t)q * G + blockIdx.x];
-  __syncthreads();
-  const unsigned cnt = cand_cnt[blockIdx.x];
-  for (unsigned i = threadIdx.x; i < cnt; i += blockDim.x) {
-    const u64 e = cand[(size_t)blockIdx.x * CAND + i];
-    const int q = (int)(e >> 32);
-    if (q >= q_lo && q <= qm) wake_ord[atomicAdd(&cur[q - q_lo], 1u)] = (int)(unsigned)e;
-  }
-}
-
-// One block, after the preparation: decides whether the rounds run (ctrl->setup), writes the
+// One block, after the preparation: the wake buckets' offsets (qscan) and, when there are at most
+// PLAN_BLOCKS preparation blocks, what k_qbucket_scan and k_place_window do for more of them: the exclusive
+// scan of each bucket's counts over the blocks, and the first window from the blocks' candidates (one
+// cursor per bucket serves all blocks: the order inside a bucket is free).  Four dependent launches of one
+// small block each cost 4 to 5 us apiece.
+//
+// Then it decides whether the rounds run (ctrl->setup), writes the
 // initial round state into both slots, clears the steps' queue counters and statistics, and
 // writes the round kernels' argument block: the host's arguments completed with what only the
 // device knows (Delta, the rounds bound, the vertices with arcs), first step 1.  When the rounds
 // are not to run, both slots say "done" (enqueued steps return at once) and the report is written
-// here.
-__global__ void k_setup(RoundCtx c, LaunchBlock* lb, int qpath) {
-  if (blockIdx.x != 0) return;
-  for (int i = threadIdx.x; i < 3 * 16; i += blockDim.x) c.qcnt[i] = 0;
-  for (int i = threadIdx.x; i < RT; i += blockDim.x) c.ex_part[i] = 0;
+// here.  The control block of the next call, if there is one, is cleared for it.
+__global__ __launch_bounds__(1024) void k_plan(RoundCtx c, LaunchBlock* lb, int qpath, int fused,
+                                               unsigned* __restrict__ mat, const unsigned* __restrict__ tot,
+                                               const u64* __restrict__ cand, const unsigned* __restrict__ cand_cnt,
+                                               int* __restrict__ qoff, int* __restrict__ next_ne, Ctrl* next) {
+  __shared__ unsigned tq[QCAP], cur[QCAP];
+  const int tid = threadIdx.x, G = c.prep_blocks;
+  if (qpath && qpath_ok(c.ctrl)) {  // uniform
+    const int D = (int)(c.ctrl->delta >> FIX);
+    for (int q = tid; q <= D; q += 1024) {
+      unsigned acc = 0;
+      if (fused) {
+        unsigned x[PLAN_BLOCKS];
+#pragma unroll
+        for (int b = 0; b < PLAN_BLOCKS; ++b) x[b] = b < G && q <= c.qmax[b] ? mat[(size_t)q * G + b] : 0u;
+#pragma unroll
+        for (int b = 0; b < PLAN_BLOCKS; ++b) {
+          if (b < G && q <= c.qmax[b]) mat[(size_t)q * G + b] = acc;
+          acc += x[b];
+        }
+      } else {
+        acc = tot[q];
+      }
+      tq[q] = acc;
+    }
+    __syncthreads();
+    qscan(D, tq, cur, qoff, next_ne);
+    __syncthreads();
+    if (fused) {
+      const int q_lo = (int)c.ctrl->place_lo;
+      for (int i = tid; i < G * CAND; i += 1024) {
+        if (i % CAND < (int)cand_cnt[i / CAND]) {
+          const u64 e = cand[i];
+          const int q = (int)(e >> 32);
+          if (q >= q_lo && q <= D) c.wake_ord[atomicAdd(&cur[q], 1u)] = (int)(unsigned)e;
+        }
+      }
+    }
+  }
+  if (next)
+    for (int i = tid; i < (int)(sizeof(Ctrl) / sizeof(u64)); i += 1024) reinterpret_cast<u64*>(next)[i] = 0;
+  for (int i = tid; i < 3 * 16; i += 1024) c.qcnt[i] = 0;
+  c.ex_part[tid] = 0;
+  static_assert(RT == 1024, "a statistics slot per thread");
   if (threadIdx.x != 0) return;
   Ctrl* ctrl = c.ctrl;
   const u64 delta = ctrl->delta, n_active = ctrl->n_active;

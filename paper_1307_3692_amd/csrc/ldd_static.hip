@@ -167,13 +167,9 @@ ldd_status run_static(DeviceState& d, const ldd_csr* g, const int64_t* shift_fix
                      (unsigned*)(b + LAY.cand_cnt));
   if (o.validate && nnz > 0)
     hipLaunchKernelGGL(k_check_cols, dim3(grid_for(nnz, 256, 4096)), dim3(256), 0, st, n, nnz, g->col_idx, ctrl);
-  hipLaunchKernelGGL(k_qbucket_scan, dim3(std::min(QCAP, 1024)), dim3(256), 0, st, gp, (unsigned*)(b + LAY.mat),
-                     (const int*)(b + LAY.qmax), (unsigned*)(b + LAY.hist), (const Ctrl*)ctrl);
-  hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), 0, st, (const Ctrl*)ctrl, (const unsigned*)(b + LAY.hist),
-                     (int*)(b + LAY.wake_off), (int*)(b + LAY.next_ne));
-  hipLaunchKernelGGL(k_place_window, dim3(gp), dim3(256), 0, st, (const Ctrl*)ctrl, (const unsigned*)(b + LAY.mat),
-                     (const int*)(b + LAY.qmax), (const int*)(b + LAY.wake_off), (const u64*)(b + LAY.cand),
-                     (const unsigned*)(b + LAY.cand_cnt), (int*)(b + LAY.wake_ord));
+  if (gp > PLAN_BLOCKS)
+    hipLaunchKernelGGL(k_qbucket_scan, dim3(std::min(QCAP, 1024)), dim3(256), 0, st, gp, (unsigned*)(b + LAY.mat),
+                       (const int*)(b + LAY.qmax), (unsigned*)(b + LAY.hist), (const Ctrl*)ctrl);
   ST_TRY(hipGetLastError());
 
   RoundCtx c{};
@@ -208,7 +204,13 @@ ldd_status run_static(DeviceState& d, const ldd_csr* g, const int64_t* shift_fix
   c.tail_min_left = 16;
   c.ex_part = (u64*)(b + LAY.ex_part);
   c.report = rep_dev;
-  hipLaunchKernelGGL(k_setup, dim3(1), dim3(256), 0, st, c, lb, 1);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, st, c, lb, 1, gp <= PLAN_BLOCKS ? 1 : 0, (unsigned*)(b + LAY.mat),
+                     (const unsigned*)(b + LAY.hist), (const u64*)(b + LAY.cand), (const unsigned*)(b + LAY.cand_cnt),
+                     (int*)(b + LAY.wake_off), (int*)(b + LAY.next_ne), (Ctrl*)nullptr);
+  if (gp > PLAN_BLOCKS)
+    hipLaunchKernelGGL(k_place_window, dim3(gp), dim3(256), 0, st, (const Ctrl*)ctrl, (const unsigned*)(b + LAY.mat),
+                       (const int*)(b + LAY.qmax), (const int*)(b + LAY.wake_off), (const u64*)(b + LAY.cand),
+                       (const unsigned*)(b + LAY.cand_cnt), (int*)(b + LAY.wake_ord));
   ST_TRY(hipGetLastError());
 
   int blocks = o.blocks > 0 ? o.blocks : 2 * d.num_cu;
