@@ -79,43 +79,57 @@ __device__ __forceinline__ u64 shfl_u64(u64 v, int src) {
   return ((u64)hi << 32) | lo;
 }
 
-__device__ __forceinline__ u64 wave_min_u64(u64 v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)v, o, WAVE);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, WAVE);
-    u64 w = ((u64)hi << 32) | lo;
-    v = w < v ? w : v;
-  }
+// Wave reductions and scans (all 64 lanes must be active) by data-parallel-primitive moves between
+// lanes: within rows of 16 lanes, then the last lane of a row into the next, then that of the lower half
+// into the upper.  A move through LDS (__shfl) takes some 60 ns and a reduction of 64 bits is 12 of them,
+// one after another: the two at the end of a round step that had nothing to do were 2.3 us of it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_u32(unsigned v, unsigned none) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u64 dpp_u64(u64 v, u64 none) {
+  const unsigned lo = dpp_u32<CTRL, ROWS>((unsigned)v, (unsigned)none);
+  const unsigned hi = dpp_u32<CTRL, ROWS>((unsigned)(v >> 32), (unsigned)(none >> 32));
+  return ((u64)hi << 32) | lo;
+}
+// inclusive scan over the lanes by op, whose neutral element is `none`
+template <class Op>
+__device__ __forceinline__ u64 wave_scan_u64(u64 v, u64 none, const Op& op) {
+  v = op(v, dpp_u64<0x111, 0xf>(v, none));  // row_shr:1, 2, 4, 8
+  v = op(v, dpp_u64<0x112, 0xf>(v, none));
+  v = op(v, dpp_u64<0x114, 0xf>(v, none));
+  v = op(v, dpp_u64<0x118, 0xf>(v, none));
+  v = op(v, dpp_u64<0x142, 0xa>(v, none));  // row_bcast:15 into rows 1 and 3
+  v = op(v, dpp_u64<0x143, 0xc>(v, none));  // row_bcast:31 into rows 2 and 3
   return v;
+}
+__device__ __forceinline__ u64 last_lane_u64(u64 v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, WAVE - 1);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), WAVE - 1);
+  return ((u64)hi << 32) | lo;
+}
+
+__device__ __forceinline__ u64 wave_min_u64(u64 v) {
+  return last_lane_u64(wave_scan_u64(v, ~0ull, [](u64 a, u64 b) { return b < a ? b : a; }));
 }
 
 __device__ __forceinline__ u64 wave_sum_u64(u64 v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)v, o, WAVE);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, WAVE);
-    v += ((u64)hi << 32) | lo;
-  }
-  return v;
+  return last_lane_u64(wave_scan_u64(v, 0ull, [](u64 a, u64 b) { return a + b; }));
 }
 
 __device__ __forceinline__ u64 wave_max_u64(u64 v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)v, o, WAVE);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, WAVE);
-    u64 w = ((u64)hi << 32) | lo;
-    v = w > v ? w : v;
-  }
-  return v;
+  return last_lane_u64(wave_scan_u64(v, 0ull, [](u64 a, u64 b) { return b > a ? b : a; }));
 }
 
-// inclusive prefix sum over the wave (all 64 lanes must be active)
+// inclusive prefix sum over the wave
 __device__ __forceinline__ unsigned wave_incl_scan(unsigned x) {
-  const unsigned lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < WAVE; d <<= 1) {
-    unsigned y = __shfl_up(x, d, WAVE);
-    if (lane >= (unsigned)d) x += y;
-  }
+  x += dpp_u32<0x111, 0xf>(x, 0);
+  x += dpp_u32<0x112, 0xf>(x, 0);
+  x += dpp_u32<0x114, 0xf>(x, 0);
+  x += dpp_u32<0x118, 0xf>(x, 0);
+  x += dpp_u32<0x142, 0xa>(x, 0);
+  x += dpp_u32<0x143, 0xc>(x, 0);
   return x;
 }
 

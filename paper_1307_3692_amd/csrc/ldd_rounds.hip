@@ -166,25 +166,25 @@ __device__ __forceinline__ void phase_wake(const RoundCtx& c, int r, int k, Appe
     hi = c.wake_off[r + 1];
   }
   const int cnt = hi - lo;
-  for (long long base = (long long)blockIdx.x * RT; base < cnt; base += (long long)gridDim.x * RT) {
+  // from the grid's last block downwards: the expansion's tiles start at its first one, so on small
+  // rounds the two chains of dependent loads run side by side
+  for (long long base = (long long)(gridDim.x - 1 - blockIdx.x) * RT; base < cnt; base += (long long)gridDim.x * RT) {
     const long long i = base + threadIdx.x;
     bool want = false;
     int v = 0;
     unsigned deg = 0;
     if (i < cnt) {
       v = c.wake_ord[lo + i];
-      const u64 sv = (u64)c.shift[v];
+      const u64 sv = (u64)c.shift[v], pv = c.P[v];
       // in bucket D - r: wakes now iff frac <= dfrac; in bucket D - r - 1: iff frac > dfrac
       const bool wakes = !c.wake_q || ((lo + i >= mid) ? (sv & FMASK) <= dfrac : (sv & FMASK) > dfrac);
       const u64 self = ((c.delta - sv) << c.B) | (u64)v;
-      if (wakes && c.P[v] > self) {
+      if (wakes && pv > self) {
         const u64 old = atomic_min_u64(&c.P[v], self);
+        deg = degree(c, v);  // in flight with the atomic
         if (old > self) {
           wmin = self < wmin ? self : wmin;
-          if (old == INF) {
-            want = true;
-            deg = degree(c, v);
-          }
+          want = old == INF;
         }
       }
     }
@@ -197,26 +197,30 @@ __device__ __forceinline__ void phase_wake(const RoundCtx& c, int r, int k, Appe
 // a tile are staged in LDS (arc prefix, first arc in col_idx, offer); each thread finds its
 // arc's entry by binary search.  Entries have degree >= 1, so a tile whose first arc lies in
 // entry e only touches entries e .. e+RT-1.
-// TAIL = false: round step; an arc appends its far end if it is reached for the first time.
-// TAIL = true: tail sweep `sweep`; an arc appends its far end whenever it lowered the label
+// tag = 0: round step; an arc appends its far end if it is reached for the first time.
+// Else: tail sweep, whose stamp is tag; an arc appends its far end whenever it lowered the label
 // and the far end is not queued for the next sweep yet.
-template <bool TAIL>
 __device__ __forceinline__ void phase_top_down(const RoundCtx& c, int k, const int* qv, const unsigned* qa, unsigned nf, unsigned af,
-                               AppendBuf& ab, StepShared& sh, u64& wmin, unsigned sweep) {
+                               AppendBuf& ab, StepShared& sh, u64& wmin, unsigned tag) {
   unsigned* w_pre = sh.w_pre;
   int* w_first = sh.w_first;
   u64* w_offer = sh.w_offer;
   const u64 unit = (u64)1 << (FIX + c.B);
-  const unsigned G = gridDim.x;
+  // no more blocks than tiles
+  const unsigned tiles = (af + RT - 1) / RT, G = tiles < gridDim.x ? tiles : gridDim.x;
+  if (blockIdx.x >= G) return;
   const unsigned a_begin = (unsigned)(((u64)af * blockIdx.x) / G);
   const unsigned a_end = (unsigned)(((u64)af * (blockIdx.x + 1)) / G);
   if (a_begin >= a_end) return;
-  if (threadIdx.x < WAVE) {  // last entry with qa <= a_begin
-    const unsigned e = wave_search_le(qa, nf, a_begin);
-    if (threadIdx.x == 0) sh.start = e;
+  unsigned ent = 0;
+  if (blockIdx.x > 0) {
+    if (threadIdx.x < WAVE) {  // last entry with qa <= a_begin
+      const unsigned e = wave_search_le(qa, nf, a_begin);
+      if (threadIdx.x == 0) sh.start = e;
+    }
+    __syncthreads();
+    ent = sh.start;
   }
-  __syncthreads();
-  unsigned ent = sh.start;
   for (unsigned tile = a_begin; tile < a_end; tile += RT) {
     for (int kk = threadIdx.x; kk <= RT; kk += RT) {
       const unsigned e = ent + kk;
@@ -239,7 +243,7 @@ __device__ __forceinline__ void phase_top_down(const RoundCtx& c, int k, const i
     int w = 0;
     unsigned deg = 0;
     if (a < a_end) {
-      int lo = 0, hi = RT;  // last kk in [0, RT) with w_pre[kk] <= a
+      int lo = 0, hi = min(RT, (int)(nf - ent));  // last kk in [0, hi) with w_pre[kk] <= a
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (w_pre[mid] <= a) lo = mid;
@@ -255,19 +259,13 @@ __device__ __forceinline__ void phase_top_down(const RoundCtx& c, int k, const i
       if ((unsigned)w < (unsigned)c.n) {
         if (c.P[w] > offer) {
           const u64 old = atomic_min_u64(&c.P[w], offer);
+          deg = degree(c, w);  // in flight with the atomic
           if (old > offer) {
-            if (TAIL) {
-              const unsigned tag = c.stamp_base + sweep + 1;
-              if (__hip_atomic_fetch_max(&c.stamp[w], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tag) {
-                want = true;
-                deg = degree(c, w);
-              }
+            if (tag) {
+              want = __hip_atomic_fetch_max(&c.stamp[w], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tag;
             } else {
               wmin = offer < wmin ? offer : wmin;
-              if (old == INF) {
-                want = true;
-                deg = degree(c, w);
-              }
+              want = old == INF;
             }
           }
         }
@@ -278,6 +276,7 @@ __device__ __forceinline__ void phase_top_down(const RoundCtx& c, int k, const i
     block_append(ab, want, w, deg, c, k);
     // the entry holding the next tile's first arc is one of ent .. ent+RT (all staged)
     const unsigned next = tile + RT;
+    if (next >= a_end) break;
     __syncthreads();
     if (threadIdx.x == 0) {
       int lo = 0, hi = RT + 1;
@@ -370,6 +369,30 @@ __device__ __attribute__((noinline)) unsigned pull_rows_wave(const RoundCtx& c, 
   return examined;
 }
 
+// Arcs a .. a_cap of row v until the best offer reaches L_r: the first alone (most rows stop there), then
+// four per group, their column ids, then their labels, so that a group costs two dependent loads.
+__device__ __forceinline__ void pull_arcs(const RoundCtx& c, int v, int a0, int a_cap, u64 Lr, u64 prev_round, u64 unit,
+                                          int& a, u64& best, bool& bad, unsigned& examined) {
+  while (a < a_cap && best > Lr && !bad) {
+    const int lim = min(a_cap, a + (a == a0 ? 1 : 4));
+    int u[4];
+    u64 pu[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = a + j < lim ? c.col[a + j] : v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bad |= (unsigned)u[j] >= (unsigned)c.n;
+      pu[j] = a + j < lim && (unsigned)u[j] < (unsigned)c.n ? load_u64_relaxed(&c.P[u[j]]) : INF;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((pu[j] >> (FIX + c.B)) == prev_round && pu[j] != INF && pu[j] + unit < best) best = pu[j] + unit;
+    examined += (unsigned)(lim - a);
+    a = lim;
+  }
+  if (bad) atomic_or_u32(&c.ctrl->err, ERR_BAD_COL);
+}
+
 template <bool SEED>
 __device__ __forceinline__ void phase_pull(const RoundCtx& c, int r, int k, u64 Lr, AppendBuf& ab, StepShared& sh,
                                            u64& wmin, u64& examined_total) {
@@ -378,13 +401,21 @@ __device__ __forceinline__ void phase_pull(const RoundCtx& c, int r, int k, u64 
   const u64 unit = (u64)1 << (FIX + B);
   const u64 base_r = (u64)r << (FIX + B);
   const u64 prev_round = (u64)(r - 1);
-  const long long stride = (long long)gridDim.x * RT;
+  // 64 rows per wave and tile; fewer where that leaves waves without any, since a wave finishes its
+  // long rows one after another (R-MAT 12: the first pull 15 -> 6 us)
+  int rows = WAVE;
+  while (rows > 1 && (long long)(rows / 2) * NW * gridDim.x >= c.n) rows /= 2;
+  const long long stride = (long long)gridDim.x * NW * rows;
+  const int lane = (int)lane_id();
+  const long long wave = rows == WAVE ? (long long)blockIdx.x * NW + threadIdx.x / WAVE
+                                      : (long long)(threadIdx.x / WAVE) * gridDim.x + blockIdx.x;
+  const long long first = lane < rows ? wave * rows + lane : c.n;
   // each tile's labels are loaded during the tile before, so that the load is in flight across
   // the append's barriers (a label read early can only be higher than the current one: labels
   // only drop, so the worst case is a pull that finds nothing to lower)
-  u64 pv_next = (long long)blockIdx.x * RT + threadIdx.x < c.n ? c.P[blockIdx.x * RT + threadIdx.x] : 0;
-  for (long long base = (long long)blockIdx.x * RT; base < c.n; base += stride) {
-    const long long vi = base + threadIdx.x;
+  u64 pv_next = first < c.n ? c.P[first] : 0;
+  for (long long base = 0; base < c.n; base += stride) {  // uniform over the grid
+    const long long vi = first < c.n ? base + first : c.n;
     const int v = (int)vi;
     bool want = false, defer = false;
     unsigned deg = 0;
@@ -397,23 +428,13 @@ __device__ __forceinline__ void phase_pull(const RoundCtx& c, int r, int k, u64 
           int a = a0;
           bool bad = false;
           const int a_cap = a1 - a0 > PULL_CAP ? a0 + PULL_CAP : a1;
-          for (; a < a_cap && best > Lr; ++a) {
-            ++examined;
-            const int u = c.col[a];
-            if ((unsigned)u >= (unsigned)c.n) {
-              atomic_or_u32(&c.ctrl->err, ERR_BAD_COL);
-              bad = true;
-              break;
-            }
-            const u64 pu = load_u64_relaxed(&c.P[u]);
-            if ((pu >> (FIX + B)) == prev_round && pu != INF && pu + unit < best) best = pu + unit;
-          }
+          pull_arcs(c, v, a0, a_cap, Lr, prev_round, unit, a, best, bad, examined);
           if (!bad && a < a1 && best > Lr) {  // long row, undecided: the wave finishes it below
             defer = true;
             sh.w_pre[threadIdx.x] = (unsigned)a;
             sh.w_first[threadIdx.x] = a1;
             sh.w_offer[threadIdx.x] = best;
-          } else if (best < pv) {
+          } else if (!bad && best < pv) {
             pull_update<SEED>(c, v, best, a1 - a0, wmin, want, deg);
           }
         }
@@ -479,17 +500,7 @@ __device__ __forceinline__ void phase_seed(const RoundCtx& c, int r, int k, u64 
         int a = a0;
         bool bad = false;
         const int a_cap = a1 - a0 > PULL_CAP ? a0 + PULL_CAP : a1;
-        for (; a < a_cap && best > Lr; ++a) {
-          ++examined;
-          const int u = c.col[a];
-          if ((unsigned)u >= (unsigned)c.n) {
-            atomic_or_u32(&c.ctrl->err, ERR_BAD_COL);
-            bad = true;
-            break;
-          }
-          const u64 pu = load_u64_relaxed(&c.P[u]);
-          if ((pu >> (FIX + B)) == prev_round && pu != INF && pu + unit < best) best = pu + unit;
-        }
+        pull_arcs(c, v, a0, a_cap, Lr, prev_round, unit, a, best, bad, examined);
         if (!bad && a < a1 && best > Lr) {  // long row, undecided: the wave finishes it below
           defer = true;
           sh.w_pre[threadIdx.x] = (unsigned)a;
@@ -520,17 +531,6 @@ __device__ __forceinline__ int choose_dir(const RoundCtx& c, int dir, u64 nf, u6
   const bool bu_better = af * (u64)c.td_to_bu > unsettled_arcs + (u64)c.n / 4;
   if (dir == DIR_TD) return bu_better ? DIR_BU : DIR_TD;
   return (bu_better || nf * (u64)c.bu_to_td >= (u64)c.n) ? DIR_BU : DIR_TD;
-}
-
-// State of step k from the state of step k-1 and what step k-1 appended.
-// The state is read with coherent loads: in the persistent kernel it was written by another
-// block during the previous step.
-__device__ RoundState load_state(const RoundState* p) {
-  RoundState s;
-#define LDD_LOAD(f) s.f = __hip_atomic_load(&p->f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  LDD_STATE_FIELDS(LDD_LOAD)
-#undef LDD_LOAD
-  return s;
 }
 
 template <int SCOPE>
@@ -577,37 +577,34 @@ __device__ __forceinline__ void phase_place(const RoundCtx& c, long long placed_
   }
 }
 
-__device__ __forceinline__ RoundState next_state(const RoundCtx& c, int k) {
-  const RoundState P = load_state(&c.st[(k - 1) & 1]);
-  const u64 out = load_u64_relaxed(qcounter(c, k - 1));
-  RoundState S = P;
+// The state of step k in place of that of step k-1, which queued `out`.
+__device__ __forceinline__ void next_state(const RoundCtx& c, int k, RoundState& S, u64 out) {
+  const long long mode = S.mode, round = S.round;
   S.seq = k;
-  if (P.mode == MODE_DONE) return S;
-  if (P.mode == MODE_PLACE) {
-    // step k-1 placed buckets [lo, placed_lo) and queued nothing: round P.round runs now, on
+  if (mode == MODE_PLACE) {
+    // step k-1 placed buckets [lo, placed_lo) and queued nothing: round S.round runs now, on
     // the queue step k-2 wrote (hence the parity flip), unless it needs still lower buckets
-    S.placed_lo = P.placed_lo > ABUF ? P.placed_lo - ABUF : 0;
-    S.flip = P.flip ^ 1;
-    S.mode = needs_place(c, (int)S.round, S.placed_lo) ? MODE_PLACE : MODE_ROUNDS;
-    return S;
+    S.placed_lo = S.placed_lo > ABUF ? S.placed_lo - ABUF : 0;
+    S.flip ^= 1;
+    S.mode = needs_place(c, (int)round, S.placed_lo) ? MODE_PLACE : MODE_ROUNDS;
+    return;
   }
   const unsigned nf = min((unsigned)(out >> 32), (unsigned)c.n), af = (unsigned)out;
-  if (P.mode == MODE_ROUNDS) {
+  if (mode == MODE_ROUNDS) {
     int next_r;
     if (k > 1) {
       S.settled += nf;
       S.unsettled_arcs -= af;
       S.rounds += 1;
-      if (P.prev >> 32) {
-        S.td_rounds += P.dir == DIR_TD;
-        S.bu_rounds += P.dir == DIR_BU;
+      if (S.prev >> 32) {
+        S.td_rounds += S.dir == DIR_TD;
+        S.bu_rounds += S.dir == DIR_BU;
       }
       S.max_frontier = (long long)nf > S.max_frontier ? (long long)nf : S.max_frontier;
-      next_r = nf ? (int)P.round + 1 : c.next_ne[P.round + 1];
+      next_r = nf ? (int)round + 1 : c.next_ne[round + 1];
     } else {
       next_r = c.next_ne[0];
     }
-    S.prev = (long long)out;
     const u64 left = c.n_active - (u64)S.settled;
     if ((u64)S.settled >= c.n_active) {
       S.mode = MODE_DONE;
@@ -620,19 +617,19 @@ __device__ __forceinline__ RoundState next_state(const RoundCtx& c, int k) {
       S.tail_round = next_r;
     } else {
       S.round = next_r;
-      S.dir = nf ? choose_dir(c, (int)P.dir, nf, af, (u64)S.unsettled_arcs) : P.dir;
+      if (nf) S.dir = choose_dir(c, (int)S.dir, nf, af, (u64)S.unsettled_arcs);
       if (needs_place(c, next_r, S.placed_lo)) S.mode = MODE_PLACE;
     }
-  } else {  // MODE_TAIL: step k-1 ran sweep P.round and queued `out`
+  } else {  // MODE_TAIL: step k-1 ran sweep `round` and queued `out`
     S.tail_iters += 1;
-    S.round = P.round + 1;
-    S.prev = (long long)out;
+    S.round = round + 1;
     if (nf == 0) S.mode = MODE_DONE;
   }
-  return S;
+  S.prev = (long long)out;
 }
 
-// per-block statistics slot: no atomics (each block owns its slot for the whole call)
+// per-block statistics slot (each block owns its slot for the whole call; an atomic that returns nothing
+// is not waited for)
 __device__ __forceinline__ void add_examined(const RoundCtx& c, u64 examined, StepShared& sh) {
   examined = wave_sum_u64(examined);
   __syncthreads();
@@ -641,26 +638,40 @@ __device__ __forceinline__ void add_examined(const RoundCtx& c, u64 examined, St
   if (threadIdx.x == 0) {
     u64 t = 0;
     for (int w = 0; w < NW; ++w) t += sh.red[w];
-    if (t) c.ex_part[blockIdx.x] += t;
+    if (t) (void)__hip_atomic_fetch_add(&c.ex_part[blockIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 // One step; returns the mode it ran in (MODE_DONE: nothing was left to do).
 __device__ __forceinline__ int round_step(const RoundCtx& c, int k, AppendBuf& ab, StepShared& sh,
                                           unsigned short* slist) {
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < WAVE) {
+    // One lane per word of the state (coherent loads, all in flight together: in the persistent kernel
+    // another block wrote it during the previous step), the other slot's mode and the queue's counter.
     // Once a step has written "done" into either slot no step writes a slot again, so later
     // steps only need the two mode words to leave.
-    const bool done = __hip_atomic_load(&c.st[0].mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == MODE_DONE ||
-                      __hip_atomic_load(&c.st[1].mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == MODE_DONE;
-    if (done) {
-      sh.S.mode = MODE_DONE;
-      sh.S.seq = -1;
-    } else {
-      sh.S = next_state(c, k);
+    constexpr int W = sizeof(RoundState) / 8, MODE_WORD = offsetof(RoundState, mode) / 8;
+    static_assert(W + 2 <= WAVE, "a lane per word");
+    const int t = (int)threadIdx.x;
+    const u64* prev = reinterpret_cast<const u64*>(&c.st[(k - 1) & 1]);
+    const u64* from = t < W ? prev + t : (t == W ? reinterpret_cast<const u64*>(&c.st[k & 1].mode) : qcounter(c, k - 1));
+    const u64 x = t < W + 2 ? load_u64_relaxed(from) : 0;
+    if (t < W) reinterpret_cast<u64*>(&sh.S)[t] = x;
+    const u64 out = shfl_u64(x, W + 1);
+    const bool done = shfl_u64(x, MODE_WORD) == MODE_DONE || shfl_u64(x, W) == MODE_DONE;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (t == 0) {
+      if (done) {
+        sh.S.mode = MODE_DONE;
+        sh.S.seq = -1;
+      } else {
+        next_state(c, k, sh.S, out);
+      }
+      ab.n = 0;
+      ab.arcs = 0;
     }
-    ab.n = 0;
-    ab.arcs = 0;
   }
   __syncthreads();
   // the fields the step uses, as wave-uniform scalars (the rest of the state stays in LDS)
@@ -712,26 +723,24 @@ __device__ __forceinline__ int round_step(const RoundCtx& c, int k, AppendBuf& a
     if (threadIdx.x == 0) sh.lr = m == INF ? INF : m + ((u64)1 << (FIX + c.B));
     __syncthreads();
   }
+  unsigned tag = 0;
+  bool push = nf != 0;
   if (mode == MODE_ROUNDS) {
-    const int r = round;
-    phase_wake(c, r, k, ab, wmin);
-    if (nf) {
-      if (dir == DIR_BU) {
-        phase_pull<false>(c, r, k, sh.lr, ab, sh, wmin, examined);
-      } else {
-        phase_top_down<false>(c, k, qv, qa, nf, af, ab, sh, wmin, 0);
-        if (blockIdx.x == 0 && threadIdx.x == 0) examined += af;
-      }
+    phase_wake(c, round, k, ab, wmin);
+    if (nf && dir == DIR_BU) {
+      phase_pull<false>(c, round, k, sh.lr, ab, sh, wmin, examined);
+      push = false;
     }
+  } else if (round == 0) {
+    phase_seed(c, __builtin_amdgcn_readfirstlane((int)sh.S.tail_round), k, nf ? sh.lr : INF, ab, sh, slist, wmin,
+               examined);
+    push = false;
   } else {
-    const unsigned sweep = (unsigned)round;
-    if (sweep == 0) {
-      phase_seed(c, __builtin_amdgcn_readfirstlane((int)sh.S.tail_round), k, nf ? sh.lr : INF, ab, sh, slist, wmin,
-                 examined);
-    } else if (nf) {
-      phase_top_down<true>(c, k, qv, qa, nf, af, ab, sh, wmin, sweep);
-      if (blockIdx.x == 0 && threadIdx.x == 0) examined += af;
-    }
+    tag = c.stamp_base + (unsigned)round + 1;
+  }
+  if (push) {
+    phase_top_down(c, k, qv, qa, nf, af, ab, sh, wmin, tag);
+    if (blockIdx.x == 0 && threadIdx.x == 0) examined += af;
   }
   block_flush(ab, c, k);
   const u64 bm = block_min_u64(wmin, sh);
@@ -930,6 +939,16 @@ __device__ __forceinline__ void slot_carry(A* a, B* b) {
       if (b) b[t + 1] += b[w * WAVE];
     }
   }
+}
+
+// The state is read with coherent loads: in the persistent kernel it was written by another
+// block during the previous step.
+__device__ RoundState load_state(const RoundState* p) {
+  RoundState s;
+#define LDD_LOAD(f) s.f = __hip_atomic_load(&p->f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  LDD_STATE_FIELDS(LDD_LOAD)
+#undef LDD_LOAD
+  return s;
 }
 
 // Start of step k, round r (one lane per slot): each slot's mode for this step and, in
