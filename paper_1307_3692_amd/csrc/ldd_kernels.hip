@@ -802,8 +802,9 @@ __global__ __launch_bounds__(256) void k_cut(int n, const int* __restrict__ row_
         const unsigned e = ent + kk;
         if (e < nl) {
           const int v = lv[e];
-          const bool ok = (unsigned)v < (unsigned)n;
-          w_pre[kk] = la[e];
+          const unsigned pre = la[e];
+          const bool ok = (unsigned)v < (unsigned)n && pre < tile + T;  // entries past the tile: the prefix alone
+          w_pre[kk] = pre;
           w_first[kk] = ok ? row_ptr[v] : 0;
           w_c[kk] = ok ? centre[v] : -1;
         } else {

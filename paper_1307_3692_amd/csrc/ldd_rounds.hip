@@ -196,7 +196,8 @@ __device__ __forceinline__ void phase_wake(const RoundCtx& c, int r, int k, Appe
 // Each block walks its arc range in tiles of RT arcs.  The RT+1 queue entries that can touch
 // a tile are staged in LDS (arc prefix, first arc in col_idx, offer); each thread finds its
 // arc's entry by binary search.  Entries have degree >= 1, so a tile whose first arc lies in
-// entry e only touches entries e .. e+RT-1.
+// entry e only touches entries e .. e+RT-1; of those past the tile only the prefix is read (row offsets
+// and labels are random accesses, and a tile of rows of 16 arcs has 64 entries).
 // tag = 0: round step; an arc appends its far end if it is reached for the first time.
 // Else: tail sweep, whose stamp is tag; an arc appends its far end whenever it lowered the label
 // and the far end is not queued for the next sweep yet.
@@ -226,8 +227,9 @@ __device__ __forceinline__ void phase_top_down(const RoundCtx& c, int k, const i
       const unsigned e = ent + kk;
       if (e < nf) {
         const int u = qv[e];
-        w_pre[kk] = qa[e];
-        const bool ok = (unsigned)u < (unsigned)c.n;
+        const unsigned pre = qa[e];
+        w_pre[kk] = pre;
+        const bool ok = (unsigned)u < (unsigned)c.n && pre < tile + RT;  // entries past the tile: the prefix alone
         w_first[kk] = ok ? c.row_ptr[u] : 0;
         const u64 pu = ok ? load_u64_relaxed(&c.P[u]) : INF;
         w_offer[kk] = pu == INF ? INF : pu + unit;
@@ -1137,9 +1139,10 @@ __device__ __forceinline__ void srv_td_segment(const RoundCtx& c, int k, SrvAppe
       const unsigned e = ent + kk;
       if (e < nf) {
         const int u = qv[e];
-        w_pre[kk] = qa[e];
+        const unsigned pre = qa[e];
+        w_pre[kk] = pre;
         const long long lu = (long long)u - vbeg;
-        const bool ok = lu >= 0 && lu < n;
+        const bool ok = lu >= 0 && lu < n && pre < tile + RT;  // entries past the tile: the prefix alone
         w_first[kk] = ok ? rp[lu] : 0;
         const u64 pu = ok ? load_u64_relaxed(&c.P[u]) : INF;
         w_offer[kk] = pu == INF ? INF : pu + unit;

@@ -44,7 +44,8 @@ constexpr int MAX_BATCH = 16;         // requests per admission / finishing laun
 // most arcs of the requests on the device at once (32-bit arc offsets of a step's top-down split)
 constexpr unsigned long long MAX_ACTIVE_ARCS = 0xffffffffull;
 constexpr int ADM_T = 1024;           // threads of the admission kernels
-constexpr int FIN_T = 256;            // threads of the finishing kernel (its arc tile)
+constexpr int FIN_T = 256;            // threads of the finishing kernels (the cut's arc tile)
+constexpr int FIN_SUB = 8;            // vertices per thread and pass of the first
 constexpr unsigned ERR_ROUNDS = 64u;  // the request needs more rounds than the server takes
 constexpr unsigned ROW_ERRS = ERR_BAD_SHIFT | ERR_BAD_ROWPTR;
 
@@ -304,8 +305,9 @@ __global__ __launch_bounds__(ADM_T) void k_adm_place(AdmBatch b, int max_rounds,
 // The cut counts the arcs whose ends have different centres, twice per cut edge.  With H the
 // piece of the request's hub, an edge between H and the rest is cut, an edge inside H is not:
 // so only the rows outside H are read.  An arc from outside H into H counts 2 (its reverse is
-// not read), an arc between two vertices outside H counts 1 if their centres differ (its
-// reverse counts the other 1).  RMAT-like requests have almost all arcs inside H.
+// not read), an edge between two vertices outside H counts 2 from its smaller end if their centres
+// differ.  RMAT-like requests have almost all arcs inside H; in the others the cut is bound by the
+// random reads of the far ends' bits and labels, the latter left out at the larger end.
 
 // Vertex chunks aligned to 64 vertices (the slot starts on a multiple of 64), so every bitmap
 // word belongs to one block of one request.
@@ -315,7 +317,9 @@ __device__ __forceinline__ long long chunk64(long long n, int j, int nb) {
 
 // Centres (request-local ids) into the caller's buffer, the bit of H of every vertex, and the
 // rows outside H with arcs, listed (local id, arc prefix) in the slot's range of one queue pair
-// (a request found done has nothing queued and is never expanded again).
+// (a request found done has nothing queued and is never expanded again).  One reservation per 2048 vertices:
+// the counters of a batch share lines, and an atomic on one line takes 12 ns, so that one per 256 was most of
+// the time (over a burst of 64 requests 1.00 ms, and 0.63 now; the cut 1.31 and 1.01).
 __global__ __launch_bounds__(FIN_T) void k_fin_vertices(FinBatch b, int B, const u64* __restrict__ P,
                                                         const SlotInfo* __restrict__ slots,
                                                         const u64* __restrict__ adm_hub, u64* __restrict__ hbits,
@@ -332,32 +336,48 @@ __global__ __launch_bounds__(FIN_T) void k_fin_vertices(FinBatch b, int B, const
   const long long hv = t.vbeg + (long long)(adm_hub[t.slot] & 0xffffffffull);
   const u64 hubc = P[hv] == INF ? (u64)hv : (P[hv] & mask);
   const unsigned lane = lane_id(), wid = threadIdx.x / WAVE;
-  for (long long v0 = lo; v0 < hi; v0 += FIN_T) {  // uniform trip count over the block
-    const long long v = v0 + threadIdx.x;
-    bool out = false;
-    unsigned deg = 0;
-    bool inH = false;
+  for (long long b0 = lo; b0 < hi; b0 += FIN_T * FIN_SUB) {  // uniform trip count over the block
+    const long long v0 = b0 + (long long)wid * WAVE * FIN_SUB + lane;
     // loads first, at an index clamped into the chunk, so that they need no branch
-    const long long vc = v < hi ? v : hi - 1;
-    const u64 p = P[t.vbeg + vc];
-    const u64 c = p == INF ? (u64)(t.vbeg + vc) : (p & mask);  // INF: isolated, its own centre
-    const int r0 = t.rp[vc], r1 = t.rp[vc + 1];
-    if (v < hi) {
-      t.centre[v] = ran ? (int)(c - (u64)t.vbeg) : -1;
-      deg = (unsigned)(r1 - r0);
-      inH = c == hubc;
-      out = ran && !inH && deg > 0;
+    u64 p[FIN_SUB];
+    int r0[FIN_SUB];
+    unsigned deg[FIN_SUB], rank[FIN_SUB], pre[FIN_SUB];
+#pragma unroll
+    for (int i = 0; i < FIN_SUB; ++i) {
+      const long long v = v0 + i * WAVE, vc = v < hi ? v : hi - 1;
+      p[i] = P[t.vbeg + vc];
+      r0[i] = t.rp[vc];
+      deg[i] = (unsigned)t.rp[vc + 1];
     }
-    const u64 hb = __ballot(inH);
-    if (lane == 0 && v0 + wid * WAVE < hi) hbits[(t.vbeg + v0 + wid * WAVE) >> 6] = hb;
-    const u64 om = __ballot(out);
-    const unsigned incl = wave_incl_scan(out ? deg : 0u);
-    if (lane == WAVE - 1) {
-      w_cnt[wid] = (unsigned)__popcll(om);
-      w_arcs[wid] = incl;
+    unsigned out = 0, wc = 0, wa = 0;
+#pragma unroll
+    for (int i = 0; i < FIN_SUB; ++i) {
+      const long long v = v0 + i * WAVE;
+      const u64 c = p[i] == INF ? (u64)(t.vbeg + v) : (p[i] & mask);  // INF: isolated, its own centre
+      bool inH = false, o = false;
+      deg[i] -= (unsigned)r0[i];
+      if (v < hi) {
+        t.centre[v] = ran ? (int)(c - (u64)t.vbeg) : -1;
+        inH = c == hubc;
+        o = ran && !inH && deg[i] > 0;
+      }
+      const u64 hb = __ballot(inH);
+      if (lane == 0 && v < hi) hbits[(t.vbeg + v) >> 6] = hb;
+      const u64 om = __ballot(o);
+      const unsigned d = o ? deg[i] : 0u, incl = wave_incl_scan(d);
+      out |= (unsigned)o << i;
+      rank[i] = wc + rank_below(om);
+      pre[i] = wa + incl - d;
+      wc += (unsigned)__popcll(om);
+      wa += (unsigned)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+    }
+    if (lane == 0) {
+      w_cnt[wid] = wc;
+      w_arcs[wid] = wa;
     }
     __syncthreads();
     unsigned bc = 0, ba = 0, tc = 0, ta = 0;
+#pragma unroll
     for (int w = 0; w < NWF; ++w) {
       if (w < (int)wid) {
         bc += w_cnt[w];
@@ -369,11 +389,14 @@ __global__ __launch_bounds__(FIN_T) void k_fin_vertices(FinBatch b, int B, const
     if (tc) {  // uniform
       if (threadIdx.x == 0) base = atomic_add_u64(&lcnt[t.slot], ((u64)tc << 32) | ta);
       __syncthreads();
-      if (out) {
-        const unsigned idx = (unsigned)(base >> 32) + bc + rank_below(om);
-        const unsigned pre = (unsigned)base + ba + incl - deg;
-        list_v[t.vbeg + idx] = (int)v;
-        list_a[t.vbeg + idx] = pre;
+      bc += (unsigned)(base >> 32);
+      ba += (unsigned)base;
+#pragma unroll
+      for (int i = 0; i < FIN_SUB; ++i) {
+        if ((out >> i) & 1) {
+          list_v[t.vbeg + bc + rank[i]] = (int)(v0 + i * WAVE);
+          list_a[t.vbeg + bc + rank[i]] = ba + pre[i];
+        }
       }
     }
     __syncthreads();
@@ -390,6 +413,7 @@ __global__ __launch_bounds__(FIN_T) void k_fin_cut(FinBatch b, int B, const u64*
   __shared__ unsigned w_pre[T + 1];
   __shared__ int w_first[T + 1];
   __shared__ u64 w_c[T + 1];
+  __shared__ int w_v[T + 1];
   __shared__ unsigned s_ent;
   __shared__ u64 red[T / WAVE];
   const FinItem& t = b.it[item_of(b, blockIdx.x)];
@@ -414,13 +438,17 @@ __global__ __launch_bounds__(FIN_T) void k_fin_cut(FinBatch b, int B, const u64*
         const unsigned e = ent + kk;
         if (e < ne) {
           const int v = LV[e];
-          w_pre[kk] = LA[e];
-          w_first[kk] = t.rp[v];
-          w_c[kk] = Ps[v] & mask;
+          const unsigned pre = LA[e];
+          const bool in = pre < tile + T;  // entries past the tile: the prefix alone
+          w_pre[kk] = pre;
+          w_first[kk] = in ? t.rp[v] : 0;
+          w_c[kk] = in ? Ps[v] & mask : 0;
+          w_v[kk] = v;
         } else {
           w_pre[kk] = na;
           w_first[kk] = 0;
           w_c[kk] = 0;
+          w_v[kk] = 0;
         }
       }
       __syncthreads();
@@ -436,7 +464,7 @@ __global__ __launch_bounds__(FIN_T) void k_fin_cut(FinBatch b, int B, const u64*
         if ((unsigned)wl < (unsigned)t.n) {  // (a request with a bad column id fails anyway)
           const long long w = t.vbeg + wl;  // arena id
           if ((hbits[w >> 6] >> (w & 63)) & 1) cut += 2;
-          else cut += (P[w] & mask) != w_c[lo];
+          else if (wl > w_v[lo]) cut += 2 * (unsigned)((P[w] & mask) != w_c[lo]);
         }
       }
       const unsigned next = tile + T;
