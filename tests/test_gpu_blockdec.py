@@ -46,3 +46,21 @@ def test_block_decomposition_equals_oracle(ldd):
     shifts = [inputs.make_shifts(900, 0.5, 3 + L) for L in range(2)]
     want, run, placed = oracle.block_decomposition(rp, ci, shifts)
     assert len(edges) == 2 and np.array_equal(lv.cpu().numpy(), want) and np.any(want < 0)
+
+
+@pytest.mark.parametrize("leaves", [31, 32, 33, 63, 256, 1023, 1024, 1025, 2600])
+def test_row_lengths(ldd, leaves):
+    """Rows walked by a lane (up to 32 arcs), by a wave (up to 1024) and by the workgroup, in every level: hubs
+    whose leaves are also on a ring, so that pieces split the hubs' rows."""
+    import torch
+    hubs = 5
+    n = hubs * (leaves + 1)
+    hub = np.repeat(np.arange(hubs) * (leaves + 1), leaves)
+    leaf = hub + 1 + np.tile(np.arange(leaves), hubs)
+    rp, ci = inputs.from_edges(n, np.concatenate([hub, np.arange(n)]), np.concatenate([leaf, (np.arange(n) + 1) % n]))
+    lv, edges = ldd.block_decompose(torch.from_numpy(rp).cuda(), torch.from_numpy(ci).cuda(), beta=0.6, seed=leaves,
+                                    max_levels=64)
+    shifts = [inputs.make_shifts(n, 0.6, leaves + L) for L in range(len(edges))]
+    want, run, placed = oracle.block_decomposition(rp, ci, shifts)
+    assert run == len(edges) and placed == edges
+    assert np.array_equal(lv.cpu().numpy(), want)
