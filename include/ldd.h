@@ -72,7 +72,7 @@ typedef struct {
 enum { LDD_DIR_AUTO = 0, LDD_DIR_TOP_DOWN = 1, LDD_DIR_BOTTOM_UP = 2 };
 /* Round engine: one persistent kernel with grid barriers, one launch per round step over the
  * whole GPU, one workgroup running every round of the graph (workgroup barriers only), or a team
- * of workgroups (blocks of them, default one per CU, at most the workgroups that can be resident
+ * of workgroups (blocks of them, by default by the size of the graph, at most the workgroups that can be resident
  * at once) running every round with a barrier in device memory per round or per few rounds (top-down only:
  * for large graphs of low degree and many rounds, such as grids).  AUTO: a graph of more than 7 arcs
  * per vertex on average, or a call with direction LDD_DIR_BOTTOM_UP, takes the launch engine; a
@@ -92,7 +92,7 @@ typedef struct {
   int32_t engine;         /* LDD_ENGINE_*                                                 */
   int32_t validate;       /* 1: check CSR monotonicity on the device before running       */
   int32_t blocks;         /* workgroups of the round kernel (0 = 2 per CU; the workgroup batch engine
-                             and a team: 1 per CU, a team at most the workgroups that can be resident
+                             1 per CU; a team 0.35 times the root of n up to 1 per CU, at most the workgroups that can be resident
                              at once, one per CU; at most 1024)                                               */
   int32_t td_to_bu;       /* switch to bottom-up when frontier arcs * td_to_bu > unsettled arcs (0 = default 14) */
   int32_t bu_to_td;       /* switch back when frontier vertices * bu_to_td < n (0 = default 24)                 */

@@ -694,7 +694,7 @@ static int tail_den_of(const ldd_options& o) {
 }
 
 // One graph on the workgroup engine: one workgroup (WORKGROUP), or a team of K workgroups
-// (TEAM: blocks of them, default one per CU, at most the workgroups that can be resident at once, at
+// (TEAM: blocks of them, by default by the size of the graph up to one per CU, at most the workgroups that can be resident at once, at
 // least 64 vertices per member) meeting at a device-memory barrier once per round.
 static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t* shift_fix, int32_t* centre,
                                   int64_t* cut_edges, const ldd_options& opt, ldd_stats* stats, hipStream_t st,
@@ -705,7 +705,10 @@ static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t*
   if (s != LDD_OK) return s;
   int K = 1;
   if (team) {
-    K = opt.blocks > 0 ? opt.blocks : w.num_cu;
+    // Members by default: a step's work goes with n / K and its barrier with K, so the best K goes with the
+    // root of n (Erdos-Renyi, degree 5 to 7, us at K = 64, 128, 192, 256: 40000 vertices 150, 160, 170, 183; 200000
+    // 231, 204, 205, 215; a million 584, 417, 394, 384; geometric graphs the same)
+    K = opt.blocks > 0 ? opt.blocks : std::min(w.num_cu, std::max(32, (int)(0.35 * std::sqrt((double)n))));
     K = std::min(K, std::min(w.block_coresident, TEAM_GROUP * TEAM_GROUPS));
     K = std::min(K, n / 64);
     K = std::max(K, 1);
