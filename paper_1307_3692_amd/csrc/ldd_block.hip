@@ -1715,7 +1715,7 @@ __device__ __forceinline__ void team_entry(const BlockJob& j, BlockShared& sh, g
 // its label drops.  A sweep appends a vertex once (its stamp takes the tag).  All threads call; returns
 // the queue's length.
 template <bool SWEEP>
-__device__ __attribute__((noinline)) unsigned team_step1(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
+__device__ __forceinline__ unsigned team_step1(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
                                                          int r, int D, bool first_only, int tag, u64& examined) {
   const BlockJob j = job_of(sh);
   const int n = j.n;
@@ -1822,7 +1822,7 @@ struct SeenOffers {
 // empty; offers stay below r + rounds all the same (an entry of the queue lies below r), so no
 // vertex is given a label above its own one before its wake round.
 template <bool SWEEP>
-__device__ __attribute__((noinline)) unsigned team_steps(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
+__device__ __forceinline__ unsigned team_steps(BlockShared& sh, g_cint* cur, g_int* nxt, unsigned e0, unsigned e1,
                                                          int r, int D, int rounds, u64& examined) {
   const BlockJob j = job_of(sh);
   const int n = j.n;

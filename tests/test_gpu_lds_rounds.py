@@ -103,3 +103,11 @@ def test_graph_in_lds(ldd, n, degree):
     ed.append(5 + 2 * np.arange(1, degree - 1) % n)
     rp, ci = inputs.from_edges(n, np.concatenate(es), np.concatenate(ed) % n)
     check(ldd, rp, ci, inputs.make_shifts(n, 0.02, n + degree), dict(engine=3), dict(engine=3, tail_vertices=-1))
+
+
+@pytest.mark.parametrize("n,degree,beta", [(20_000, 5.0, 0.2), (90_000, 6.5, 0.08), (150_000, 3.2, 0.2)])
+def test_team_tail_from_a_large_frontier(ldd, n, degree, beta):
+    """The last rounds' frontier outweighs the vertices left: the tail takes over from it."""
+    rp, ci = inputs.er(n, degree, n)
+    check(ldd, rp, ci, inputs.make_shifts(n, beta, 6), dict(engine=4), dict(engine=4, blocks=7), dict(engine=4, blocks=256),
+          dict(engine=4, tail_vertices=4), dict(engine=4, tail_vertices=-1))
