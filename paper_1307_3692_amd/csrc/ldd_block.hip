@@ -58,7 +58,11 @@ struct HeavyRow {
   int a0, deg;
 };
 
+constexpr int FIX_LONG_ROWS = 544;  // long rows of a graph held whole in LDS
+
 struct BlockShared {
+  unsigned nlong;
+  unsigned short longv[FIX_LONG_ROWS];
   BlockJob j;                // the job in hand
   int woff[BLOCK_WCAP + 1];  // wake bucket offsets (exclusive prefix), then the scatter cursors
   u64 starts[BNW][WALK_WORDS];  // per wave: which of its arcs start a row (walk_rows)
@@ -1241,6 +1245,10 @@ __device__ void block_graph(BlockShared& sh, BlockOut* out) {
 // 61 us, 46 of them this kernel.  Two or eight passes between barriers measure the same within 2 us.
 constexpr int FIX_V = 6;
 constexpr int FIX_BLOCK = 4;  // passes between two barriers
+// A row of more than FIX_LONG arcs is relaxed by a wave, 64 arcs at a time, not by its thread arc after arc
+// (R-MAT 11, 4 edges per vertex: 518 us with each hub's row on one thread, and 167; R-MAT 10: 269 and 82).
+constexpr int FIX_LONG = 64;
+static_assert(BLOCK_LDS_BYTES / 4 / FIX_LONG <= FIX_LONG_ROWS, "every long row can be listed");
 
 struct FixGraph {
   u64* P;           // LDS: labels
@@ -1248,6 +1256,8 @@ struct FixGraph {
   const int* col;
   int n, degmax, B;
   u64 unit;
+  const unsigned short* longv;  // LDS: the vertices of long rows
+  int nlong;
 };
 
 // The passes and the output.  Passes run FIX_BLOCK at a time with no barrier between them (in-place
@@ -1266,7 +1276,7 @@ __device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u
 #pragma unroll
   for (int k = 0; k < FIX_V; ++k) {
     const int v = tid + k * BT, a0 = v < n ? rp[v] : 0, a1 = v < n ? rp[v + 1] : 0;
-    p[k] = v < n ? P[v] : 0;
+    p[k] = v < n && a1 - a0 <= FIX_LONG ? P[v] : 0;  // 0: never lowered here
 #pragma unroll
     for (int e = 0; e < RD / 2; ++e) {
       const int x = a0 + 2 * e < a1 ? col[a0 + 2 * e] : v, y = a0 + 2 * e + 1 < a1 ? col[a0 + 2 * e + 1] : v;
@@ -1289,7 +1299,7 @@ __device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u
             const u64 m = q < t ? q : t;
             best = m < best ? m : best;
           }
-          if (rest) {
+          if (rest && p[k]) {
             const int a1 = rp[v + 1];
             for (int a = rp[v] + RD; a < a1; ++a) {
               const u64 q = P[col[a]];
@@ -1305,6 +1315,7 @@ __device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u
       }
       for (int v = tid + FIX_V * BT; v < n; v += BT) {
         const int a1 = rp[v + 1];
+        if (a1 - rp[v] > FIX_LONG) continue;
         const u64 own = P[v];
         u64 best = own;
         for (int a = rp[v]; a < a1; ++a) {
@@ -1313,6 +1324,19 @@ __device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u
         }
         if (best < own) {
           P[v] = best;
+          changed = 1;
+        }
+      }
+      for (int t = tid / WAVE; t < g.nlong; t += BT / WAVE) {  // one wave each: the only writer of the label
+        const int v = g.longv[t], a1 = rp[v + 1];
+        u64 best = INF;
+        for (int a = rp[v] + (int)lane_id(); a < a1; a += WAVE) {
+          const u64 q = P[col[a]];
+          best = q < best ? q : best;
+        }
+        best = wave_min_u64(best) + g.unit;
+        if (best < P[v]) {
+          if (lane_id() == 0) P[v] = best;
           changed = 1;
         }
       }
@@ -1330,7 +1354,12 @@ __device__ __forceinline__ void fix_passes(const FixGraph& g, g_int* centre, g_u
     labels[v] = q;
     *pieces += c == v;
     const int a1 = rp[v + 1];
+    if (a1 - rp[v] > FIX_LONG) continue;
     for (int a = rp[v]; a < a1; ++a) *cut2 += (int)(P[col[a]] & mask) != c;
+  }
+  for (int t = tid / WAVE; t < g.nlong; t += BT / WAVE) {
+    const int v = g.longv[t], c = (int)(P[v] & mask), a1 = rp[v + 1];
+    for (int a = rp[v] + (int)lane_id(); a < a1; a += WAVE) *cut2 += (int)(P[col[a]] & mask) != c;
   }
   *passes_out = passes;
   *converged_out = converged;
@@ -1347,7 +1376,7 @@ __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, Block
   u64* P = reinterpret_cast<u64*>(blk_dyn);
   int* lrp = reinterpret_cast<int*>(P + n);
   int* lcol = lrp + n + 1;
-  if (tid == 0) sh.err = 0;
+  if (tid == 0) sh.err = sh.nlong = 0;
   __syncthreads();
   unsigned err = 0;
   u64 dmax = 0;
@@ -1375,6 +1404,11 @@ __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, Block
         lrp[v] = a0[k];
         P[v] = (u64)s[k];  // the shift, until Delta is known
         active += deg[k] > 0;
+        if (deg[k] > FIX_LONG && !err) {  // (offsets that are no offsets may claim more of them than there can be)
+          const unsigned i = atomicAdd(&sh.nlong, 1u);
+          if (i < (unsigned)FIX_LONG_ROWS) sh.longv[i] = (unsigned short)v;
+          else err |= ERR_BAD_ROWPTR;
+        }
         degmax = deg[k] > 0 && (u64)deg[k] > degmax ? (u64)deg[k] : degmax;
         dmax = (u64)s[k] > dmax ? (u64)s[k] : dmax;
       }
@@ -1412,7 +1446,7 @@ __device__ __attribute__((noinline)) void block_graph_fix(BlockShared& sh, Block
   }
   for (int v = tid; v < n; v += BT) P[v] = ((delta - P[v]) << B) | (u64)v;
   __syncthreads();
-  const FixGraph g{P, lrp, lcol, n, (int)degmax, B, (u64)1 << (FIX + B)};
+  const FixGraph g{P, lrp, lcol, n, (int)degmax, B, (u64)1 << (FIX + B), sh.longv, (int)sh.nlong};
   long long passes = 0;
   bool converged = false;
   u64 cut2 = 0, pieces = 0;

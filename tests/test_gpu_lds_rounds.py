@@ -92,8 +92,8 @@ def test_frontier_explodes_inside_a_step(ldd, tail):
 
 
 # one graph held whole in LDS: four arcs of a vertex are in registers, eight, or eight and the rest read
-# from LDS; six vertices of a thread are, further ones are not; and one size past the LDS
-@pytest.mark.parametrize("degree", [4, 5, 8, 9, 300])
+# from LDS, and above 64 a wave has the row; six vertices of a thread are, further ones are not; and one size past the LDS
+@pytest.mark.parametrize("degree", [4, 5, 8, 9, 64, 65, 300])
 @pytest.mark.parametrize("n", [301, 1023, 1025, 6144, 6145, 7300])
 def test_graph_in_lds(ldd, n, degree):
     """A ring with one vertex of the given degree and a few of four."""
