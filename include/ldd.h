@@ -74,9 +74,10 @@ enum { LDD_DIR_AUTO = 0, LDD_DIR_TOP_DOWN = 1, LDD_DIR_BOTTOM_UP = 2 };
  * whole GPU, one workgroup running every round of the graph (workgroup barriers only), or a team
  * of workgroups (blocks of them, by default by the size of the graph, at most the workgroups that can be resident
  * at once) running every round with a barrier in device memory per round or per few rounds (top-down only:
- * for large graphs of low degree and many rounds, such as grids).  AUTO: a graph of more than 7 arcs
- * per vertex on average, or a call with direction LDD_DIR_BOTTOM_UP, takes the launch engine; a
- * sparser graph takes one workgroup when it has at most 2^15 arcs and 2^14 vertices, else a team, unless
+ * for large graphs of low degree and many rounds, such as grids).  AUTO: a call with direction
+ * LDD_DIR_BOTTOM_UP takes the launch engine; a graph of at most 2^14 vertices and 2^15 arcs (3 * 2^14 arcs
+ * when it has more than 7 per vertex on average) takes one workgroup; of the others one of more than 7 arcs
+ * per vertex takes the launch engine and a sparser one a team, unless
  * a vertex has more than 4096 arcs (the team finds it in its preparation and the call continues on the
  * launch engine).  ldd_tune may pick any of them. */
 enum {

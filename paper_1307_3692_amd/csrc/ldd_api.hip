@@ -652,12 +652,15 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
 // ------------------------------------------------------------------------------------------
 // the workgroup engine for one graph: one workgroup runs all rounds (small graphs)
 // ------------------------------------------------------------------------------------------
-// The automatic engine choice.  Graphs of more than AUTO_TEAM_DEGREE arcs per vertex on average
+// The automatic engine choice.  A small graph, of at most BLOCK_AUTO_VERTICES vertices and BLOCK_AUTO_ARCS
+// arcs (BLOCK_AUTO_DENSE of more than AUTO_TEAM_DEGREE per vertex), runs in one workgroup (us, launch
+// engine -> workgroup: Erdos-Renyi of 300 / 1000 / 2500 vertices of degree 9 115 -> 39, 127 -> 45, 173 -> 68; R-MAT
+// 8 / 9 / 10 / 11, 16 edges per vertex 121 -> 71, 118 -> 63, 124 -> 109, 129 -> 101; R-MAT 12 with 8 edges, 53496 arcs,
+// 136 -> 135, with 16, 96776 arcs, 135 -> 170).  Else graphs of more than AUTO_TEAM_DEGREE arcs per vertex on average
 // (RMAT and other skewed graphs, random graphs of small diameter) go to the multi-block engines,
 // whose bottom-up pulls and grid-wide arc splits they need.  Sparser graphs (meshes, geometric and
-// road-like graphs: many rounds with small frontiers) go to one workgroup when they have at most
-// BLOCK_AUTO_ARCS arcs and BLOCK_AUTO_VERTICES vertices (one workgroup reads them faster than round steps
-// over the whole GPU synchronise; but its preparation and output take 1.8 ns a vertex, against 55 us for a
+// road-like graphs: many rounds with small frontiers) go to one workgroup when they are small
+// (one workgroup reads them faster than round steps over the whole GPU synchronise; but its preparation and output take 1.8 ns a vertex, against 55 us for a
 // team's on 262,144 vertices, so few arcs on many vertices, the late levels of a block decomposition, take
 // 0.12 ms on a team and 0.7 ms alone), else to a team, which refuses a graph with a vertex of more than
 // AUTO_TEAM_DEG_CAP arcs (one member would expand it alone), and that graph goes to the multi-block engines
@@ -668,6 +671,7 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
 // diameter, huge frontiers, where the top-down team reads every arc) 4M/8M vertices 1.0/1.3 ->
 // 1.4/3.6 (50K/200K: 0.28/0.32 -> 0.16/0.20), and RMAT 10-20 0.18-0.30 -> 0.3-36.
 constexpr long long BLOCK_AUTO_ARCS = 1ll << 15;
+constexpr long long BLOCK_AUTO_DENSE = 3ll << 14;
 constexpr int BLOCK_AUTO_VERTICES = 1 << 14;
 constexpr long long AUTO_TEAM_DEGREE = 7;
 constexpr int AUTO_TEAM_DEG_CAP = 4096;
@@ -798,10 +802,11 @@ static ldd_status decompose_impl(Workspace& w, const ldd_csr* g, const int64_t* 
                                  int64_t* cut_edges, const ldd_options& o, ldd_stats* stats, hipStream_t st,
                                  const BatchView* bv) {
   // a forced bottom-up policy needs the multi-block engines (the workgroup engines run top-down)
-  const bool sparse = g->nnz <= AUTO_TEAM_DEGREE * (long long)g->n && o.direction != LDD_DIR_BOTTOM_UP;
-  const bool small = g->nnz <= BLOCK_AUTO_ARCS && g->n <= BLOCK_AUTO_VERTICES;
-  const bool auto_wg = o.engine == LDD_ENGINE_AUTO && sparse && small;
-  const bool auto_team = o.engine == LDD_ENGINE_AUTO && sparse && !small;
+  const bool top_down = o.direction != LDD_DIR_BOTTOM_UP;
+  const bool sparse = g->nnz <= AUTO_TEAM_DEGREE * (long long)g->n;
+  const bool small = g->nnz <= (sparse ? BLOCK_AUTO_ARCS : BLOCK_AUTO_DENSE) && g->n <= BLOCK_AUTO_VERTICES;
+  const bool auto_wg = o.engine == LDD_ENGINE_AUTO && top_down && small;
+  const bool auto_team = o.engine == LDD_ENGINE_AUTO && top_down && sparse && !small;
   if (!bv && (o.engine == LDD_ENGINE_WORKGROUP || o.engine == LDD_ENGINE_TEAM || auto_wg || auto_team)) {
     const bool team = o.engine == LDD_ENGINE_TEAM || auto_team;
     ldd_status s = decompose_block(w, g, shift_fix, centre, cut_edges, o, stats, st, team,

@@ -111,3 +111,10 @@ def test_team_tail_from_a_large_frontier(ldd, n, degree, beta):
     rp, ci = inputs.er(n, degree, n)
     check(ldd, rp, ci, inputs.make_shifts(n, beta, 6), dict(engine=4), dict(engine=4, blocks=7), dict(engine=4, blocks=256),
           dict(engine=4, tail_vertices=4), dict(engine=4, tail_vertices=-1))
+
+
+@pytest.mark.parametrize("scale,edges", [(8, 16), (10, 16), (11, 8), (11, 16), (11, 18), (12, 6), (12, 8)])
+def test_small_dense_graphs(ldd, scale, edges):
+    """Skewed graphs on both sides of the automatic choice's line, and of the size that is held whole in LDS."""
+    rp, ci = inputs.rmat(scale, edges, seed=scale + edges)
+    check(ldd, rp, ci, inputs.make_shifts(rp.size - 1, 0.1, 8), dict(), dict(engine=3), dict(direction=2))
