@@ -74,8 +74,10 @@ struct BlockShared {
   unsigned cnt3[3];          // appends: round k counts in cnt3[k % 3], so one barrier per round
   unsigned nh3[3];           // heavy rows listed, likewise
   unsigned oc3[3];           // claims: a conflict in the round, likewise
+  unsigned er3[3];           // errors the round's walks found, likewise: the next round's waves may be ahead of
+                             // one that has yet to ask whether this one failed, and all have to leave together
   unsigned maxdeg;           // alone: the largest degree
-  unsigned err;
+  unsigned err;              // the job's error bits; in a team's rounds the member's own (see terr)
   u64 delta, n_active;       // preparation results
   u64 settled, examined;     // round results
   long long rounds, sweeps;
@@ -88,6 +90,7 @@ struct BlockShared {
   unsigned tbase;            // the staged appends' place in the shared queue
   unsigned spill;            // an append of this step did not fit the LDS before its last round
   unsigned tspill;           // ... in any member (published by the last barrier)
+  unsigned terr;             // the error bits the last barrier published: what ends the rounds
   unsigned sfirst;           // vertices this member reached first in this step
   u64 tfirst;                // ... the team, in the last step
   u64 nz[BLOCK_WCAP / 64];   // non-empty wake buckets of the whole graph
@@ -394,8 +397,8 @@ __device__ __forceinline__ void row_of(g_cint* rp, int v, int* a0, int* deg) {
 
 // One row's arcs first, first + stride, ..., two at a time.
 template <class Arcs>
-__device__ __forceinline__ void walk_row(const BlockJob& j, BlockShared& sh, int a0, int deg, u64 o, int first, int stride,
-                                         const Arcs& arcs) {
+__device__ __forceinline__ void walk_row(const BlockJob& j, BlockShared& sh, int ci, int a0, int deg, u64 o, int first,
+                                         int stride, const Arcs& arcs) {
   const u64 offer[2] = {o, o};
 #pragma unroll 1
   for (int x = first; x < deg; x += 2 * stride) {
@@ -410,15 +413,15 @@ __device__ __forceinline__ void walk_row(const BlockJob& j, BlockShared& sh, int
       bad |= go[k] && (unsigned)w[k] >= (unsigned)j.n;
       go[k] = go[k] && (unsigned)w[k] < (unsigned)j.n;
     }
-    if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+    if (bad) atomicOr(&sh.er3[ci], ERR_BAD_COL);
     arcs.template run<2>(w, go, offer);
   }
 }
 
 // U passes of 64 of a wave's arcs, from word c0 of its start bits on (see walk_rows).
 template <int U, class Arcs>
-__device__ __forceinline__ void walk_pass(const BlockJob& j, BlockShared& sh, const u64* starts, int c0, int total, int& row,
-                                          int adj, u64 offer, const Arcs& arcs) {
+__device__ __forceinline__ void walk_pass(const BlockJob& j, BlockShared& sh, int ci, const u64* starts, int c0, int total,
+                                          int& row, int adj, u64 offer, const Arcs& arcs) {
   int w[U];
   bool go[U], bad = false;
   u64 off[U];
@@ -440,7 +443,7 @@ __device__ __forceinline__ void walk_pass(const BlockJob& j, BlockShared& sh, co
     bad |= go[k] && (unsigned)w[k] >= (unsigned)j.n;
     go[k] = go[k] && (unsigned)w[k] < (unsigned)j.n;
   }
-  if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+  if (bad) atomicOr(&sh.er3[ci], ERR_BAD_COL);
   arcs.template run<U>(w, go, off);
 }
 
@@ -452,7 +455,7 @@ __device__ __forceinline__ void walk_pass(const BlockJob& j, BlockShared& sh, co
 // entry(i) gives row i's first arc, degree and offer; arcs.run gets U far ends per lane with their
 // offers.  Few rows are spread over all waves, from the last one down (the round's wake runs in
 // the first).  A row of more than LONG_ROW arcs is walked by its wave alone, one of more than HUGE_ROW listed in slot
-// ci for walk_heavy.  Rows lie in [0, nnz] (checked by the preparation); columns are checked here.
+// ci for walk_heavy.  Rows lie in [0, nnz] (checked by the preparation); columns are checked here (sh.er3[ci]).
 template <class Entry, class Arcs>
 __device__ __forceinline__ void walk_rows(const BlockJob& j, BlockShared& sh, int ci, unsigned nf, const Entry& entry,
                                           const Arcs& arcs, unsigned& examined) {
@@ -476,8 +479,8 @@ __device__ __forceinline__ void walk_rows(const BlockJob& j, BlockShared& sh, in
     }
     for (u64 m = __ballot(alone); m; m &= m - 1) {
       const int src = __ffsll((long long)m) - 1;
-      walk_row(j, sh, __builtin_amdgcn_readlane(a0, src), __builtin_amdgcn_readlane(deg, src), shfl_u64(offer, src), (int)lane,
-               WAVE, arcs);
+      walk_row(j, sh, ci, __builtin_amdgcn_readlane(a0, src), __builtin_amdgcn_readlane(deg, src), shfl_u64(offer, src),
+               (int)lane, WAVE, arcs);
     }
     // rows taken elsewhere keep one arc, which is skipped (so that every row has a start)
     const bool none = alone || deg == 0;
@@ -491,10 +494,10 @@ __device__ __forceinline__ void walk_rows(const BlockJob& j, BlockShared& sh, in
     const int adj = none ? INT_MIN : a0 - pre;
     int row = 0;
     if (total <= 64) {
-      walk_pass<1>(j, sh, starts, 0, total, row, adj, offer, arcs);
+      walk_pass<1>(j, sh, ci, starts, 0, total, row, adj, offer, arcs);
     } else {
 #pragma unroll 1
-      for (int c = 0; c * 64 < total; c += 4) walk_pass<4>(j, sh, starts, c, total, row, adj, offer, arcs);
+      for (int c = 0; c * 64 < total; c += 4) walk_pass<4>(j, sh, ci, starts, c, total, row, adj, offer, arcs);
     }
   }
 }
@@ -507,7 +510,7 @@ __device__ __forceinline__ void walk_heavy(const BlockJob& j, BlockShared& sh, i
 #pragma unroll 1
   for (unsigned h = 0; h < nh; ++h) {
     const HeavyRow e = sh.heavy[h];
-    walk_row(j, sh, e.a0, e.deg, e.offer, (int)threadIdx.x, BT, arcs);
+    walk_row(j, sh, ci, e.a0, e.deg, e.offer, (int)threadIdx.x, BT, arcs);
   }
 }
 
@@ -804,7 +807,7 @@ __device__ __forceinline__ void table_clear(int slots) {
 // vertex the best offer of its neighbours in the frontier.  Labels go straight to memory (a conflict, for
 // the settling).  All threads call; ends with a barrier.
 __device__ __forceinline__ u64 pull_round(const BlockJob& j, BlockShared& sh, const Claim& c, g_cu64* wk, int nw, unsigned nf,
-                                          g_cint* cur, u64 mask, u64 unit) {
+                                          g_cint* cur, u64 mask, u64 unit, int ci) {
   const int n = j.n;
   g_cint* __restrict__ rp = j.row_ptr;
   g_cint* __restrict__ col = j.col;
@@ -855,7 +858,7 @@ __device__ __forceinline__ u64 pull_round(const BlockJob& j, BlockShared& sh, co
         }
 #pragma unroll
         for (int k = 0; k < PULL_U; ++k) best = pw[k] < best ? pw[k] : best;
-        if (bad) atomicOr(&sh.err, ERR_BAD_COL);
+        if (bad) atomicOr(&sh.er3[ci], ERR_BAD_COL);
       }
       if (best < p) lab_store<WG>(&P[v], best);
       if (best != INF) c.reach(v);
@@ -870,7 +873,7 @@ __device__ __forceinline__ u64 pull_round(const BlockJob& j, BlockShared& sh, co
 // The rounds of one prepared graph of at most CLAIM_N vertices until all are settled or the tail may
 // start (returned), with the state of block_rounds.
 __device__ __forceinline__ bool claim_rounds(const BlockJob& j, BlockShared& sh, g_int* cur, g_int* next, int& r, u64& settled,
-                                             u64& examined, long long& rounds) {
+                                             u64& examined, long long& rounds, unsigned& err) {
   const int n = j.n;
   g_u64* P = j.P;
   const int tid = threadIdx.x;
@@ -889,7 +892,7 @@ __device__ __forceinline__ bool claim_rounds(const BlockJob& j, BlockShared& sh,
     const int w0 = r <= D ? sh.woff[r] : 0, nw = r <= D ? sh.woff[r + 1] - w0 : 0;
     const Claim c{P, next, &sh.cnt3[ci], &sh.oc3[ci], (u64)r << (FIX + B), shift};
     if (nf > PULL_MIN && sh.maxdeg <= PULL_DEG && (u64)nf * PULL_X > n_active - settled)
-      examined += pull_round(j, sh, c, j.wk + w0, nw, nf, cur, mask, unit);
+      examined += pull_round(j, sh, c, j.wk + w0, nw, nf, cur, mask, unit, ci);
     else
       examined += claim_round(j, sh, c, j.wk + w0, nw, nf, cur, mask, unit, ci);
     // the round's vertices are settled: their labels to memory, their rows to the frontier's entries
@@ -923,11 +926,12 @@ __device__ __forceinline__ bool claim_rounds(const BlockJob& j, BlockShared& sh,
     }
     if (tid == 0) {
       const int old = ci == 0 ? 2 : ci - 1;
-      sh.cnt3[old] = sh.oc3[old] = sh.nh3[old] = 0;
+      sh.cnt3[old] = sh.oc3[old] = sh.nh3[old] = sh.er3[old] = 0;
     }
     __syncthreads();
+    err = sh.er3[ci];
+    if (err) break;
     ci = ci == 2 ? 0 : ci + 1;
-    if (sh.err) break;
     settled += nf;
     ++rounds;
     g_int* t = cur;
@@ -966,18 +970,19 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
   u64 settled = 0, examined = 0;
   long long rounds = 0, sweeps = 0;
   const u64 mask = ((u64)1 << B) - 1;
-  if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
-  int ci = 0;  // this round's counters: cnt3[ci], nh3[ci]; those of (ci + 2) % 3 are cleared for two rounds on
+  if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = sh.er3[tid] = 0;
+  int ci = 0;  // this round's counters: cnt3[ci], nh3[ci], er3[ci]; those of (ci + 2) % 3 are cleared for two rounds on
   int r = next_nonempty(sh, 0, D);
   bool tail = false;
+  unsigned err = 0;  // of the last round (the same in every thread)
   // after a round's barrier: its appends are the frontier; the counters of round k - 1 (read by every
   // thread before that barrier) are cleared for round k + 2
   const auto advance = [&]() {
     nf = sh.cnt3[ci];
+    err = sh.er3[ci];
     if (tid == 0) {
       const int old = ci == 0 ? 2 : ci - 1;
-      sh.cnt3[old] = 0;
-      sh.nh3[old] = 0;
+      sh.cnt3[old] = sh.nh3[old] = sh.er3[old] = 0;
     }
     ci = ci == 2 ? 0 : ci + 1;
     g_int* t = cur;
@@ -987,9 +992,9 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
   };
   const bool claims = n <= CLAIM_N;
   if (claims) {
-    tail = claim_rounds(j, sh, cur, next, r, settled, examined, rounds);
+    tail = claim_rounds(j, sh, cur, next, r, settled, examined, rounds, err);
     __syncthreads();
-    if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
+    if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = sh.er3[tid] = 0;
     __syncthreads();
   }
   while (!claims && settled < n_active && r <= D + n && rounds <= (long long)D + n + 2) {
@@ -997,7 +1002,7 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
     const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
     examined += alone_round<false>(j, sh, j.wk + w0, w1 - w0, nf, b, cur, mask, unit, 0, ci, app);
     advance();
-    if (sh.err) break;
+    if (err) break;
     settled += nf;
     ++rounds;
     if (nf) ++r;
@@ -1007,7 +1012,7 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
       break;
     }
   }
-  if (tail && !sh.err) {
+  if (tail) {
     // seed: F_{r-1} is the frontier (final labels); every unreached vertex with arcs takes the best of
     // its own label and its neighbours' in F_{r-1}, and is queued for the first sweep
     const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
@@ -1019,7 +1024,7 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
       for (int a = a0; a < a1; ++a) {
         const int u = col[a];
         if ((unsigned)u >= (unsigned)n) {
-          atomicOr(&sh.err, ERR_BAD_COL);
+          atomicOr(&sh.er3[ci], ERR_BAD_COL);
           break;
         }
         const u64 pu = wg_load(&P[u]);
@@ -1033,7 +1038,7 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
     __syncthreads();
     advance();
     // sweeps: sweep k relaxes the labels queued by the step before and queues those that drop
-    for (int k = 1; nf && !sh.err && sweeps <= n; ++k) {
+    for (int k = 1; nf && !err && sweeps <= n; ++k) {
       const AloneAppend app{&sh.cnt3[ci], next, b ^ 1};
       examined += alone_round<true>(j, sh, nullptr, 0, nf, b, cur, mask, unit, -(k + 1), ci, app);
       advance();
@@ -1044,6 +1049,7 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
   __syncthreads();
   examined = block_sum64(examined, sh);
   if (tid == 0) {
+    sh.err |= err;
     sh.settled = settled;
     sh.examined = examined;
     sh.rounds = rounds;
@@ -1144,8 +1150,8 @@ __device__ __forceinline__ void output_centres(const BlockJob& j, int lo, int hi
 
 // Arcs of the rows [lo, hi) whose ends have different centres (of(v): v's centre, known once
 // output_centres is done), added to *cut2.  An arc to a vertex out of range (arcs of the last frontier were
-// not read by a round) sets ERR_BAD_COL.  The rows are walked as a frontier's: a lane per row took 0.94 ns an
-// arc, most of it idle lanes on uneven degrees.
+// not read by a round) sets ERR_BAD_COL in sh.err (by thread 0, with no barrier after it).  The rows are walked as
+// a frontier's: a lane per row took 0.94 ns an arc, most of it idle lanes on uneven degrees.
 template <class Of>
 struct CutArcs {
   const Of& of;
@@ -1161,7 +1167,7 @@ struct CutArcs {
 };
 template <class Of>
 __device__ __forceinline__ void output_cut(const BlockJob& j, BlockShared& sh, int lo, int hi, const Of& of, u64* cut2) {
-  if (threadIdx.x == 0) sh.nh3[0] = 0;
+  if (threadIdx.x == 0) sh.nh3[0] = sh.er3[0] = 0;
   __syncthreads();
   const CutArcs<Of> arcs{of, *cut2};
   unsigned examined = 0;
@@ -1174,6 +1180,8 @@ __device__ __forceinline__ void output_cut(const BlockJob& j, BlockShared& sh, i
       arcs, examined);
   __syncthreads();
   walk_heavy(j, sh, 0, arcs);
+  __syncthreads();
+  if (threadIdx.x == 0) sh.err |= sh.er3[0];
 }
 
 __device__ __attribute__((noinline)) void block_output(BlockShared& sh, BlockOut* out) {
@@ -1183,6 +1191,7 @@ __device__ __attribute__((noinline)) void block_output(BlockShared& sh, BlockOut
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const u64 mask = ((u64)1 << B) - 1;
   const unsigned e0 = sh.err | (sh.settled < sh.n_active ? ERR_WATCHDOG : 0u);
+  __syncthreads();  // every thread has read it: the passes below may add to it
   u64 cut2 = 0, pieces = 0;
   if (!e0) {
     // centres of up to 16 bits are kept in LDS (a load from L2 costs a CU 0.5 - 1 ns), others read as written
@@ -1497,7 +1506,8 @@ __device__ __forceinline__ void team_clear_next(BlockShared& sh) {
 // complete before the arrival (the waits above), and every load after the barrier is issued after
 // the wait observed gen.  A bounded wait raises ERR_BARRIER instead of hanging.  Returns the queue
 // length (and in sh.tspill, sh.tfirst the step's spill and the vertices it reached first); after an
-// error every member ORs the team's error bits into sh.err.
+// error in any member every member has the team's error bits in sh.terr and in sh.err.  The rounds end on
+// sh.terr, which changes at a barrier only: sh.err may already hold what a faster wave found in the next step.
 template <bool FULL>
 __device__ unsigned team_barrier(BlockShared& sh) {
   constexpr int RMW = FULL ? __ATOMIC_ACQ_REL : __ATOMIC_RELAXED;
@@ -1512,6 +1522,7 @@ __device__ unsigned team_barrier(BlockShared& sh) {
     const unsigned in_g = K - g * TEAM_GROUP < (unsigned)TEAM_GROUP ? K - g * TEAM_GROUP : (unsigned)TEAM_GROUP;
     const unsigned e1 = sh.epoch + 1;
     const int slot = (int)(sh.epoch % 3);
+    sh.err |= sh.er3[0] | sh.er3[1] | sh.er3[2];
     if (sh.err) __hip_atomic_fetch_or(&ts->err, sh.err, __ATOMIC_RELAXED, AG);
     constexpr int ARR = 44, SPILL = 38, ERR = 32;  // at most 32 groups or members: six bits each
     const u64 mine = (1ull << ARR) | ((u64)(sh.spill != 0) << SPILL) | ((u64)(sh.err != 0) << ERR) | (u64)sh.tcount;
@@ -1552,9 +1563,11 @@ __device__ unsigned team_barrier(BlockShared& sh) {
     if (FULL) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     unsigned nf = (unsigned)(word >> 32);
     sh.tspill = 0;
+    sh.terr = 0;
     if (nf == 0xffffffffu) {
       const unsigned e = __hip_atomic_load(&ts->err, __ATOMIC_RELAXED, AG);
-      sh.err |= e ? e : (unsigned)ERR_BARRIER;
+      sh.terr = e ? e : (unsigned)ERR_BARRIER;
+      sh.err |= sh.terr;
       nf = 0;
     } else {
       sh.tspill = nf >> 31;
@@ -1602,7 +1615,7 @@ __device__ __forceinline__ unsigned team_step_end(BlockShared& sh, int n, g_int*
   }
   if (c) team_flush<ONE>(sh, n, next, gcnt, b, c);
   const unsigned nf = team_barrier<FULL>(sh);
-  if (threadIdx.x < 3) sh.cnt3[threadIdx.x] = sh.nh3[threadIdx.x] = 0;
+  if (threadIdx.x < 3) sh.cnt3[threadIdx.x] = sh.nh3[threadIdx.x] = sh.er3[threadIdx.x] = 0;
   __syncthreads();
   return nf;
 }
@@ -1646,6 +1659,7 @@ __device__ __attribute__((noinline)) void team_prepare(BlockShared& sh) {
     sh.spill = 0;
     sh.sfirst = 0;
   }
+  if (tid < 3) sh.er3[tid] = 0;
   __syncthreads();
   u64 dmax, active, degmax;
   prepare_scan(j, sh, sh.tlo, sh.thi, sh.tm == 0, &dmax, &active, &degmax);
@@ -1970,7 +1984,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
     const unsigned before = nf;
     if (step > 1) nf = team_steps<false>(sh, cur, nxt, e0, e1, r, D, step, examined);
     else nf = team_step1<false>(sh, cur, nxt, e0, e1, r, D, clean, 0, examined);
-    if (sh.err) break;
+    if (sh.terr) break;
     settled += sh.tfirst;
     rounds += step;
     if (sh.tspill) clean = false;
@@ -1988,7 +2002,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       break;
     }
   }
-  if (tail && !sh.err) {
+  if (tail) {
     // seed over the member's slice (see block_rounds): every unreached vertex takes the best of its own
     // label and what its reached neighbours offer.  With a clean queue their offers are the only ones
     // pending (every other neighbour of the frontier is final), else the frontier stays queued too.
@@ -2035,7 +2049,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
     }
     nf = team_step_end<true, true>(sh, n, nxt, gcnt, 0, sh.cnt3[0]);
     step = 1;
-    for (int k = 1; nf && !sh.err && k <= n + 1; ++k) {
+    for (int k = 1; nf && !sh.terr && k <= n + 1; ++k) {
       g_int* t = cur;
       cur = nxt;
       nxt = t;
