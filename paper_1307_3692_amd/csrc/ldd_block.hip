@@ -1839,14 +1839,16 @@ constexpr int SEEN = 4096;  // slots, beside the queues
 static_assert(TEAM_Q_BYTES + 8 * SEEN <= BLOCK_LDS_BYTES, "");
 struct SeenOffers {
   u64 base;
-  int bits;  // of an offer's distance from base; 0: not kept (labels too wide, or of any round)
+  int bits;  // of an offer's distance from base; 0: none is kept (labels too wide, or of any round)
   __device__ static u64& at(unsigned i) { return reinterpret_cast<u64*>(blk_dyn + TEAM_Q_BYTES)[i]; }
   __device__ static void clear() {
     for (int i = threadIdx.x; i < SEEN; i += BT) at((unsigned)i) = INF;
   }
   __device__ __forceinline__ bool operator()(int w, u64 offer) const {
     const u64 off = offer - base;
-    if (!bits || off >> bits) return false;  // (an entry left over from an earlier step may offer less than base)
+    // not kept: what lies further off (an entry left over from an earlier step may offer less than base), and the
+    // furthest distance, which with 64 bits in all (B = 26) would make the highest vertices' entries an empty slot
+    if (off >= ((u64)1 << bits) - 1) return false;
     const u64 mine = (u64)((unsigned)w >> 12) << bits | off;
     const u64 old = atomicMin(&at(((unsigned)w ^ (unsigned)w >> 12) & (SEEN - 1)), mine);
     return old <= mine && old >> bits == mine >> bits;
