@@ -116,7 +116,8 @@ enum { LDD_BATCH_AUTO = 0, LDD_BATCH_SEQUENTIAL = 1, LDD_BATCH_UNION = 2, LDD_BA
 
 /* Counters of the last call (filled when a non-NULL pointer is passed). */
 typedef struct {
-  int32_t rounds;          /* rounds executed (empty rounds skipped are not counted)      */
+  int32_t rounds;          /* rounds executed (empty rounds skipped are not counted; a team counts all rounds of
+                              its steps; a small graph held whole in a workgroup's LDS, the passes over it)  */
   int32_t rounds_bound;    /* floor(Delta / 2^20) + 1                                     */
   int32_t td_rounds;       /* rounds expanded top-down                                    */
   int32_t bu_rounds;       /* rounds expanded bottom-up                                   */

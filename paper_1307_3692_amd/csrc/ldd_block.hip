@@ -1988,7 +1988,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
     else nf = team_step1<false>(sh, cur, nxt, e0, e1, r, D, clean, 0, examined);
     if (sh.terr) break;
     settled += sh.tfirst;
-    rounds += step;
+    rounds += min(step, max(0, D + 1 - r));  // a step may reach past the last round
     if (sh.tspill) clean = false;
     g_int* t = cur;
     cur = nxt;
