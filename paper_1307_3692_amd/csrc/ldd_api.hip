@@ -460,8 +460,13 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
 
   const int engine = o.engine == LDD_ENGINE_PERSISTENT ? LDD_ENGINE_PERSISTENT : LDD_ENGINE_LAUNCH;
   // two blocks per CU, but fewer on small graphs, whose steps dispatch in less time (R-MAT 12: 170 -> 160 us,
-  // R-MAT 16: 250 -> 235 us with 128 and 256 blocks; R-MAT 20 has all)
-  int blocks = o.blocks > 0 ? o.blocks : std::min(2 * w.num_cu, std::max(128, n / 256));
+  // R-MAT 16: 250 -> 235 us with 128 and 256 blocks; R-MAT 20 has all): about n / 256, doubled from 128 so that there are
+  // few sizes: each has its own launch graphs, and building them takes 80 us (Erdos-Renyi, 100000 vertices of
+  // degree 20: 182 us with 390 blocks, 180 with 512, 176 with 256)
+  int blocks = o.blocks;
+  if (blocks <= 0)
+    for (blocks = 128; blocks < 2 * w.num_cu && blocks < n / 362; blocks *= 2) {}
+  if (o.blocks <= 0 && blocks > 2 * w.num_cu) blocks = 2 * w.num_cu;
   if (blocks > RT) blocks = RT;  // the per-block minima of a step are reduced by one block
   if (engine == LDD_ENGINE_PERSISTENT && blocks > w.max_coresident) blocks = w.max_coresident;
   // rounds, placement steps, tail sweeps (each settles or lowers at least one label) and slack
