@@ -1820,12 +1820,19 @@ __device__ __forceinline__ unsigned team_step1(BlockShared& sh, g_cint* cur, g_i
 // (plus STEP_SLACK entries) and a member's share stays below STEP_SHARE, and halve otherwise; shares of at
 // most STEP_SMALL rows take up to STEP_MAX_SMALL rounds (1000^2 grid: 1.84 ms with 8, 1.58 with 16; the 256^3
 // grid's larger shares drift apart in 16: 3.7 against 3.9 ms).
+// The slack lets small frontiers through whose growth says little; two rounds from them may reach the slack times
+// the square of the degree, so above STEP_DEGREE arcs per vertex it falls with that square (0 from 23 on).  With the
+// whole slack the first waves of a dense graph went into the last round of a step from several members, each vertex
+// queued by most of them: the queue overflowed and the launch engine ran the graph again (batches of eight
+// Erdos-Renyi graphs, us: 1500 vertices of degree 50 623, and 161 now; 4000 of degree 300 577 and 321; geometric
+// graphs up to degree 40 the same).
 // MIN_SHARE: a small frontier is left to fewer members, so that each has a connected patch of it (random
 // geometric graph of 150,001 vertices: 0.65 / 0.60 / 0.58 ms at 32 / 16 / 8 rows).
 constexpr int STEP_MAX = 8, STEP_MAX_SMALL = 16, STEP_BITS = 4;
 static_assert(STEP_MAX <= 1 << STEP_BITS && STEP_MAX_SMALL <= 1 << STEP_BITS, "");
 constexpr unsigned STEP_SMALL = 64;
 constexpr unsigned STEP_SLACK = 8;
+constexpr long long STEP_DEGREE = 8;
 constexpr unsigned STEP_SHARE = 1024;
 constexpr unsigned MIN_SHARE = 8;
 
@@ -1939,10 +1946,16 @@ __device__ __forceinline__ unsigned team_steps(BlockShared& sh, g_cint* cur, g_i
   return team_step_end<false, false>(sh, n, nxt, gcnt, rounds & 1, sh.cnt3[ci]);
 }
 
-__device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K) {
+__device__ __forceinline__ unsigned step_slack(const BlockJob& j) {
+  const long long most = STEP_DEGREE * j.n;
+  const float x = j.nnz > most ? (float)most / (float)j.nnz : 1.0f;
+  return (unsigned)((float)STEP_SLACK * x * x);
+}
+
+__device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K, unsigned slack) {
   if (spill || nf > STEP_SHARE * (unsigned)K) return 1;
   const int most = nf > STEP_SMALL * (unsigned)K ? STEP_MAX : STEP_MAX_SMALL;
-  if (nf <= before + before / 2 + STEP_SLACK) return 2 * rounds < most ? 2 * rounds : most;
+  if (nf <= before + before / 2 + slack) return 2 * rounds < most ? 2 * rounds : most;
   return rounds > 1 ? rounds / 2 : 1;
 }
 
@@ -1976,6 +1989,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
   if (tid < 3) sh.cnt3[tid] = sh.nh3[tid] = 0;
   int r = team_next_nonempty(sh, 0, D);
   int step = 1;        // rounds of the next step
+  const unsigned slack = step_slack(j);
   bool clean = true;   // no entry of the queue was left over by a spill
   bool tail = false;
   // at most D / 1 steps wake, and every step moves every queued label one round on
@@ -1998,7 +2012,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       clean = true;
       r = team_next_nonempty(sh, r, D);
     }
-    step = next_rounds(step, before, nf, sh.tspill, K);
+    step = next_rounds(step, before, nf, sh.tspill, K, slack);
     if (tail_next(j, n_active, settled, nf, D - r, clean)) {
       tail = true;
       break;
@@ -2060,7 +2074,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       if (step > 1) nf = team_steps<true>(sh, cur, nxt, e0, e1, 0, 0, step, examined);
       else nf = team_step1<true>(sh, cur, nxt, e0, e1, 0, 0, false, -(k + 1), examined);
       sweeps += step;
-      step = next_rounds(step, before, nf, sh.tspill, K);
+      step = next_rounds(step, before, nf, sh.tspill, K, slack);
     }
     settled = n_active;
   }

@@ -68,6 +68,22 @@ def test_team_keeps_the_graph(ldd, graph, blocks):
     assert np.array_equal(centre.cpu().numpy(), want) and cut == want_cut
 
 
+@pytest.mark.parametrize("n,degree", [(1024, 30.0), (1500, 50.0), (1500, 100.0), (4096, 50.0)])
+@pytest.mark.parametrize("beta", [0.1, 0.4, 1.0])
+def test_team_keeps_dense_graphs(ldd, n, degree, beta):
+    """The first waves of a dense graph reach most of it within two rounds: in steps of several rounds each member
+    would queue the same vertices."""
+    rp, ci = inputs.er(n, degree, n)
+    s = inputs.make_shifts(n, beta, 4)
+    want, _, want_cut = oracle.decompose(rp, ci, s)
+    d = to_dev(rp, ci, s)
+    for blocks in (2, 4, 16):
+        print(f"n {n} degree {degree} beta {beta} blocks {blocks}", flush=True)
+        centre, cut, st = ldd.decompose(*d, beta, stats=True, engine=4, blocks=blocks)
+        assert st["steps"] == 1 and st["blocks"] == blocks
+        assert np.array_equal(centre.cpu().numpy(), want) and cut == want_cut
+
+
 @pytest.mark.parametrize("strands", [16, 64])
 @pytest.mark.parametrize("tail", [0, -1])
 def test_queue_overflow_goes_to_the_launch_engine(ldd, strands, tail):
