@@ -51,6 +51,7 @@ static_assert(LC * 24 == ALONE_Q_BYTES && TC * 40 == TEAM_Q_BYTES, "the frontier
 constexpr int LONG_ROW = 32;      // rows of more arcs are taken by a wave at once ...
 constexpr int HUGE_ROW = 4096;    // ... or, above this, listed for the whole workgroup
 constexpr unsigned HCAP = 32;     // such rows listed per round (past that a wave takes them too)
+constexpr int STEP_ROW = 1024;    // a team's steps are one round when there is a row of more arcs
 constexpr int WALK_WORDS = WAVE * LONG_ROW / 64;
 
 struct HeavyRow {
@@ -76,7 +77,7 @@ struct BlockShared {
   unsigned oc3[3];           // claims: a conflict in the round, likewise
   unsigned er3[3];           // errors the round's walks found, likewise: the next round's waves may be ahead of
                              // one that has yet to ask whether this one failed, and all have to leave together
-  unsigned maxdeg;           // alone: the largest degree
+  unsigned maxdeg;           // the largest degree (a team: if above STEP_ROW)
   unsigned err;              // the job's error bits; in a team's rounds the member's own (see terr)
   u64 delta, n_active;       // preparation results
   u64 settled, examined;     // round results
@@ -1664,7 +1665,8 @@ __device__ __attribute__((noinline)) void team_prepare(BlockShared& sh) {
   u64 dmax, active, degmax;
   prepare_scan(j, sh, sh.tlo, sh.thi, sh.tm == 0, &dmax, &active, &degmax);
   if (tid == 0) {
-    if (j.deg_cap > 0 && degmax > (u64)j.deg_cap) __hip_atomic_fetch_max(&ts->maxdeg, degmax, __ATOMIC_RELAXED, AG);
+    if (degmax > (u64)STEP_ROW || (j.deg_cap > 0 && degmax > (u64)j.deg_cap))
+      __hip_atomic_fetch_max(&ts->maxdeg, degmax, __ATOMIC_RELAXED, AG);
     if (dmax) __hip_atomic_fetch_max(&ts->delta, dmax, __ATOMIC_RELAXED, AG);
     if (active) __hip_atomic_fetch_add(&ts->active, active, __ATOMIC_RELAXED, AG);
     if (sh.err) __hip_atomic_fetch_or(&ts->err, sh.err, __ATOMIC_RELAXED, AG);
@@ -1674,10 +1676,12 @@ __device__ __attribute__((noinline)) void team_prepare(BlockShared& sh) {
   const u64 n_active = __hip_atomic_load(&ts->active, __ATOMIC_RELAXED, AG);
   unsigned e = __hip_atomic_load(&ts->err, __ATOMIC_RELAXED, AG);
   if (!e) e = range_err(j.n, delta);
-  if (!e && __hip_atomic_load(&ts->maxdeg, __ATOMIC_RELAXED, AG)) e = BLK_SKEW;
+  const u64 maxdeg = __hip_atomic_load(&ts->maxdeg, __ATOMIC_RELAXED, AG);
+  if (!e && j.deg_cap > 0 && maxdeg > (u64)j.deg_cap) e = BLK_SKEW;
   __syncthreads();
   if (tid == 0) {
     sh.err |= e;
+    sh.maxdeg = (unsigned)maxdeg;
     sh.delta = delta;
     sh.n_active = n_active;
   }
@@ -1824,8 +1828,13 @@ __device__ __forceinline__ unsigned team_step1(BlockShared& sh, g_cint* cur, g_i
 // the square of the degree, so above STEP_DEGREE arcs per vertex it falls with that square (0 from 23 on).  With the
 // whole slack the first waves of a dense graph went into the last round of a step from several members, each vertex
 // queued by most of them: the queue overflowed and the launch engine ran the graph again (batches of eight
-// Erdos-Renyi graphs, us: 1500 vertices of degree 50 623, and 161 now; 4000 of degree 300 577 and 321; geometric
+// Erdos-Renyi graphs, us: 1500 vertices of degree 50 623, and 178 now; 4000 of degree 300 577 and 327; geometric
 // graphs up to degree 40 the same).
+// A row of more than STEP_ROW arcs: one round per step.  The member that reaches such a vertex inside a step expands
+// the row and what it reaches by itself (batches of eight R-MAT graphs, us, steps of several rounds and of one: scale
+// 14 with 8 edges per vertex 1541 - 1619 and 1255 - 1286, scale 15 with 3 1142 - 1462 and 1097 - 1135; a 600 x 600 grid with a
+// vertex of 3000 arcs 1420 and 1555, with steps of one round for rows of more than 256 a 200 x 200 grid with one of 1000
+// 559 and 613).
 // MIN_SHARE: a small frontier is left to fewer members, so that each has a connected patch of it (random
 // geometric graph of 150,001 vertices: 0.65 / 0.60 / 0.58 ms at 32 / 16 / 8 rows).
 constexpr int STEP_MAX = 8, STEP_MAX_SMALL = 16, STEP_BITS = 4;
@@ -1990,6 +1999,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
   int r = team_next_nonempty(sh, 0, D);
   int step = 1;        // rounds of the next step
   const unsigned slack = step_slack(j);
+  const bool single = sh.maxdeg > (unsigned)STEP_ROW;
   bool clean = true;   // no entry of the queue was left over by a spill
   bool tail = false;
   // at most D / 1 steps wake, and every step moves every queued label one round on
@@ -2012,7 +2022,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       clean = true;
       r = team_next_nonempty(sh, r, D);
     }
-    step = next_rounds(step, before, nf, sh.tspill, K, slack);
+    step = single ? 1 : next_rounds(step, before, nf, sh.tspill, K, slack);
     if (tail_next(j, n_active, settled, nf, D - r, clean)) {
       tail = true;
       break;
@@ -2074,7 +2084,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       if (step > 1) nf = team_steps<true>(sh, cur, nxt, e0, e1, 0, 0, step, examined);
       else nf = team_step1<true>(sh, cur, nxt, e0, e1, 0, 0, false, -(k + 1), examined);
       sweeps += step;
-      step = next_rounds(step, before, nf, sh.tspill, K, slack);
+      step = single ? 1 : next_rounds(step, before, nf, sh.tspill, K, slack);
     }
     settled = n_active;
   }

@@ -84,6 +84,29 @@ def test_team_keeps_dense_graphs(ldd, n, degree, beta):
         assert np.array_equal(centre.cpu().numpy(), want) and cut == want_cut
 
 
+@pytest.mark.parametrize("leaves", [1023, 1024, 1025, 5000])
+@pytest.mark.parametrize("blocks", [3, 40])
+def test_one_round_per_step_beside_a_long_row(ldd, leaves, blocks):
+    """Paths, and a star of the given number of arcs: above 1024 a team takes one round per step, so that it counts the
+    rounds that one workgroup counts; up to there it counts whole steps."""
+    n, strands, length = 60_000 + leaves + 1, 200, 300
+    ids = np.arange(strands * length).reshape(strands, length)
+    hub = strands * length
+    src = np.concatenate([ids[:, :-1].ravel(), np.full(leaves, hub)])
+    dst = np.concatenate([ids[:, 1:].ravel(), hub + 1 + np.arange(leaves)])
+    rp, ci = inputs.from_edges(n, src, dst)
+    s = np.random.default_rng(1).integers(0, S, n).astype(np.int64)
+    s[ids[:, 0]] += 320 * S
+    want, _, want_cut = oracle.decompose(rp, ci, s)
+    d = to_dev(rp, ci, s)
+    print(f"leaves {leaves} blocks {blocks}", flush=True)
+    _, _, alone = ldd.decompose(*d, 0.1, stats=True, engine=3, tail_vertices=-1)
+    centre, cut, st = ldd.decompose(*d, 0.1, stats=True, engine=4, blocks=blocks, tail_vertices=-1)
+    assert st["steps"] == 1 and st["blocks"] == blocks
+    assert np.array_equal(centre.cpu().numpy(), want) and cut == want_cut
+    assert (st["rounds"] == alone["rounds"]) == (leaves > 1024)
+
+
 @pytest.mark.parametrize("strands", [16, 64])
 @pytest.mark.parametrize("tail", [0, -1])
 def test_queue_overflow_goes_to_the_launch_engine(ldd, strands, tail):
@@ -91,7 +114,7 @@ def test_queue_overflow_goes_to_the_launch_engine(ldd, strands, tail):
     length has to overflow; every result is exact."""
     left = 0
     for length in (14, 15, 16, 17, 31):
-        rp, ci, s = hubs_behind_paths(strands, length, 2000, length)
+        rp, ci, s = hubs_behind_paths(strands, length, 1000, length)
         want, _, want_cut = oracle.decompose(rp, ci, s)
         d = to_dev(rp, ci, s)
         centre, cut, st = ldd.decompose(*d, 0.1, stats=True, engine=4, blocks=8, tail_vertices=tail)
@@ -105,8 +128,8 @@ def test_queue_overflow_goes_to_the_launch_engine(ldd, strands, tail):
 
 
 def test_queue_overflow_in_a_batch(ldd):
-    gs = [hubs_behind_paths(16, 16, 2000, 1), (*inputs.er(9000, 6.0, 2), inputs.make_shifts(9000, 0.1, 2)),
-          hubs_behind_paths(16, 15, 2500, 3), (*inputs.grid2d(70, 60), inputs.make_shifts(4200, 0.05, 4))]
+    gs = [hubs_behind_paths(16, 16, 1000, 1), (*inputs.er(9000, 6.0, 2), inputs.make_shifts(9000, 0.1, 2)),
+          hubs_behind_paths(16, 15, 900, 3), (*inputs.grid2d(70, 60), inputs.make_shifts(4200, 0.05, 4))]
     want = [oracle.decompose(*g) for g in gs]
     vo = np.cumsum([0] + [g[0].size - 1 for g in gs])
     ao = np.cumsum([0] + [g[1].size for g in gs])
