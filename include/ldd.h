@@ -93,8 +93,9 @@ typedef struct {
   int32_t engine;         /* LDD_ENGINE_*                                                 */
   int32_t validate;       /* 1: check CSR monotonicity on the device before running       */
   int32_t blocks;         /* workgroups of the round kernel (0 = 2 per CU; the workgroup batch engine
-                             1 per CU; a team 0.35 times the root of n up to 1 per CU, at most the workgroups that can be resident
-                             at once, one per CU; at most 1024)                                               */
+                             1 per CU; a team 0.35 times the root of n, above 7 arcs per vertex times the fourth root of a seventh of
+                             them, up to 1 per CU; at most the workgroups that can be resident at once, one per
+                             CU; at most 1024)                                                                */
   int32_t td_to_bu;       /* switch to bottom-up when frontier arcs * td_to_bu > unsettled arcs (0 = default 14) */
   int32_t bu_to_td;       /* switch back when frontier vertices * bu_to_td < n (0 = default 24)                 */
   int32_t tail_vertices;  /* finish by label correction once unsettled vertices * this <= active vertices

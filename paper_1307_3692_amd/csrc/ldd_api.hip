@@ -716,8 +716,13 @@ static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t*
   if (team) {
     // Members by default: a step's work goes with n / K and its barrier with K, so the best K goes with the
     // root of n (Erdos-Renyi, degree 5 to 7, us at K = 64, 128, 192, 256: 40000 vertices 150, 160, 170, 183; 200000
-    // 231, 204, 205, 215; a million 584, 417, 394, 384; geometric graphs the same)
-    K = opt.blocks > 0 ? opt.blocks : std::min(w.num_cu, std::max(32, (int)(0.35 * std::sqrt((double)n))));
+    // 231, 204, 205, 215; a million 584, 417, 394, 384; geometric graphs the same).  Denser graphs, which only a
+    // call that asks for a team brings here, have more work per vertex (60000 vertices of degree 150 298 at 85 and 230 at
+    // 184, 150000 of degree 60 288 at 135 and 231 at 231; but 15000 of degree 150 187 at 92 and 243 at 198, so not
+    // the root of the arcs)
+    const double dense = std::max(1.0, (double)g->nnz / ((double)AUTO_TEAM_DEGREE * n));
+    const int members = (int)(0.35 * std::sqrt((double)n * std::sqrt(dense)));
+    K = opt.blocks > 0 ? opt.blocks : std::min(w.num_cu, std::max(32, members));
     K = std::min(K, std::min(w.block_coresident, TEAM_GROUP * TEAM_GROUPS));
     K = std::min(K, n / 64);
     K = std::max(K, 1);

@@ -1,9 +1,10 @@
 """GPU: a team's count of rounds stays within the bound that the shifts give, also where its last step of several
-rounds reaches past it."""
+rounds reaches past it; and its members by default."""
 import numpy as np
 import pytest
 
 import inputs
+import oracle
 from graphs import S, path
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +38,19 @@ def test_rounds_within_their_bound(ldd, kind, blocks):
     assert st["rounds"] <= st["rounds_bound"]
     if kind == "path":
         assert st["rounds"] == 4001
+
+
+@pytest.mark.parametrize("n,degree", [(5000, 6.0), (40_000, 6.0), (40_000, 20.0), (40_000, 150.0)])
+def test_default_members(ldd, n, degree):
+    """They grow with the vertices, and more slowly with the arcs per vertex beyond 7."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rp, ci = inputs.er(n, degree, 5)
+    s = inputs.make_shifts(n, 0.2, 5)
+    want, _, want_cut = oracle.decompose(rp, ci, s)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (rp, ci, s)]
+    print(f"n {n} degree {degree}", flush=True)
+    centre, cut, st = ldd.decompose(*d, 0.2, stats=True, engine=4)
+    assert np.array_equal(centre.cpu().numpy(), want) and cut == want_cut
+    k = 0.35 * n ** 0.5 * max(1.0, ci.size / (7 * n)) ** 0.25
+    assert st["steps"] == 1 and abs(st["blocks"] - min(cus, max(32, k))) < 1.5
