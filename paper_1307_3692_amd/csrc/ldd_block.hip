@@ -1059,11 +1059,34 @@ __device__ __attribute__((noinline)) void block_rounds(BlockShared& sh) {
   __syncthreads();
 }
 
+// The cut arcs of a listed row (output_slice): its vertex and centre come as its offer.
+struct CutRow {
+  const BlockJob& j;
+  u64 mask;
+  u64& cut2;
+  template <int U>
+  __device__ __forceinline__ void run(const int (&w)[U], const bool (&in)[U], const u64 (&row)[U]) const {
+    bool far[U];
+    u64 pw[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      far[k] = in[k] && w[k] > (int)(row[k] >> 32);
+      pw[k] = far[k] ? wg_load(&j.P[w[k]]) : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      cut2 += far[k] && (pw[k] == INF ? w[k] : (int)(pw[k] & mask)) != (int)(unsigned)row[k] ? 2u : 0u;
+  }
+};
+
 // Centres and cut arcs of the vertices [lo, hi), added to *cut2 and *pieces; an arc to a vertex out
 // of range (arcs of the last frontier were not read by a round) sets ERR_BAD_COL.  The graph is symmetric, so
 // an edge is looked at from its smaller end alone and counts as two arcs: the far ends' labels are what
 // bounds this pass (random accesses: with every CU busy 2.3 ns an arc, half of a random graph's
 // whole time, when both arcs loaded one).
+// A row of more than HUGE_ROW arcs is listed for the whole workgroup: a thread takes 0.36 us an arc, and the
+// members of a team waited longer than their barrier allows for one with millions.  The caller has cleared
+// slot 0 of nh3 and er3 before a barrier; all threads call, and thread 0 adds the rows' errors to sh.err last.
 __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh, int lo, int hi, u64 mask, u64* cut2,
                                              u64* pieces) {
   const int n = j.n;
@@ -1091,6 +1114,13 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
       if (v < hi) {
         j.centre[v] = c[k];
         *pieces += c[k] == v;
+      }
+      if (a1[k] - a[k] > HUGE_ROW) {
+        const unsigned h = atomicAdd(&sh.nh3[0], 1u);
+        if (h < HCAP) {
+          sh.heavy[h] = HeavyRow{(u64)(unsigned)v << 32 | (unsigned)c[k], a[k], a1[k] - a[k]};
+          a[k] = a1[k];
+        }
       }
     }
     bool bad = false;
@@ -1126,6 +1156,10 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
     }
     if (bad) atomicOr(&sh.err, ERR_BAD_COL);
   }
+  __syncthreads();
+  walk_heavy(j, sh, 0, CutRow{j, mask, *cut2});
+  __syncthreads();
+  if (threadIdx.x == 0) sh.err |= sh.er3[0];
 }
 
 // The same with the centres (at most 16 bits) kept in LDS.  Centres of the vertices [lo, hi) (INF: an isolated vertex, its own
@@ -1192,7 +1226,8 @@ __device__ __attribute__((noinline)) void block_output(BlockShared& sh, BlockOut
   const int B = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 1;
   const u64 mask = ((u64)1 << B) - 1;
   const unsigned e0 = sh.err | (sh.settled < sh.n_active ? ERR_WATCHDOG : 0u);
-  __syncthreads();  // every thread has read it: the passes below may add to it
+  if (tid == 0) sh.nh3[0] = sh.er3[0] = 0;
+  __syncthreads();  // every thread has read sh.err: the passes below may add to it
   u64 cut2 = 0, pieces = 0;
   if (!e0) {
     // centres of up to 16 bits are kept in LDS (a load from L2 costs a CU 0.5 - 1 ns), others read as written
@@ -2110,6 +2145,7 @@ __device__ __attribute__((noinline)) void team_output(BlockShared& sh, BlockOut*
   const u64 mask = ((u64)1 << B) - 1;
   const unsigned e0 = sh.err | (sh.settled < sh.n_active ? ERR_WATCHDOG : 0u);
   u64 cut2 = 0, pieces = 0;
+  if (tid == 0) sh.nh3[0] = sh.er3[0] = 0;
   team_acquire();
   if (!e0) {
     output_slice(j, sh, sh.tlo, sh.thi, mask, &cut2, &pieces);
