@@ -92,14 +92,15 @@ typedef struct {
   int32_t direction;      /* LDD_DIR_*                                                    */
   int32_t engine;         /* LDD_ENGINE_*                                                 */
   int32_t validate;       /* 1: check CSR monotonicity on the device before running       */
-  int32_t blocks;         /* workgroups of the round kernel (0 = 2 per CU; the workgroup batch engine
-                             1 per CU; a team 0.35 times the root of n, above 7 arcs per vertex times the fourth root of a seventh of
-                             them, up to 1 per CU; at most the workgroups that can be resident at once, one per
-                             CU; at most 1024)                                                                */
+  int32_t blocks;         /* workgroups of the round kernel (0 = 2 per CU, 128 or 256 below about 90000 vertices;
+                             the workgroup batch engine 1 per CU; a team 0.35 times the root of n, above 7 arcs
+                             per vertex times the fourth root of a seventh of them, 32 to 1 per CU; at most the
+                             workgroups that can be resident at once, one per CU; at most 1024)              */
   int32_t td_to_bu;       /* switch to bottom-up when frontier arcs * td_to_bu > unsettled arcs (0 = default 14) */
   int32_t bu_to_td;       /* switch back when frontier vertices * bu_to_td < n (0 = default 24)                 */
   int32_t tail_vertices;  /* finish by label correction once unsettled vertices * this <= active vertices
-                             (0 = default 32, -1 = never)                                                      */
+                             (0 = default 32, -1 = never; the workgroup engines also wait for a frontier that is
+                             small, or a team's that is large, against what is left)                         */
   int32_t batch_mode;     /* ldd_decompose_batch: LDD_BATCH_* (below)                                    */
   int32_t team_arcs;      /* workgroup batch engine: arcs per workgroup of a team (0 = default: 3/4 of all arcs over
                              the grid, at least 2^14; -1 = no teams: one workgroup per graph)                 */
@@ -109,7 +110,7 @@ typedef struct {
 /* Batch engines: AUTO = WORKGROUP (one workgroup per graph, the largest graphs first, every
  * graph's rounds with workgroup barriers only; a graph with many more arcs than a workgroup's
  * share of the batch runs on a team of up to 16 workgroups that meet at a barrier in device
- * memory once per round; a graph whose shifts span 4096 or more units of distance runs alone on
+ * memory once per step of one or more rounds; a graph whose shifts span 4096 or more units of distance runs alone on
  * the launch engine); SEQUENTIAL = one ldd_decompose per graph (the plain
  * path, for comparison); UNION = the disjoint union of all graphs on the launch engine, one
  * launch per round for all graphs. */

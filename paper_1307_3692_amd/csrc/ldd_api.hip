@@ -113,7 +113,7 @@ struct Workspace {
   int ctrl_next = 0;
   void* ctrl_clean = nullptr;
   Buf ctrl, st, qcnt, lr_part, lb, ex_part, vr;
-  // workgroup engine: queues and wake order (3 ints per vertex), jobs, order, results, job counter
+  // workgroup engine: wake order and queues (4 ints per vertex), jobs, order, results, job counter
   Buf bk_wq, bk_jobs, bk_order, bk_out, bk_cnt, bk_team, bk_sync;
   // batch: union CSR with global ids, adjusted shifts, graph of each vertex, per-graph data
   Buf b_rp, b_col, b_shift, b_gid, b_off, b_dg, b_cut;
@@ -211,12 +211,12 @@ extern "C" size_t ldd_workspace_bytes(int32_t n, int64_t nnz) {
   const size_t nv = n > 0 ? (size_t)n : 1;
   // labels 8 + two queues (4 + 4 each) + wake order 4 + tail stamp 4 = 32 bytes per vertex, the
   // piece bitmap, the preparation's per-block bucket counts and window lists, rounds arrays
-  // sized by the shift range (bounded here by 2^16 rounds) and the control block; and the
+  // sized by the shift range (bounded here by 2^16 rounds) and the control blocks; and the
   // workgroup engines' wake list and queues (16 bytes per vertex) with a team's record and the
   // result record, which one call may hold beside the rest (a team that refuses a graph)
   const size_t gp = std::min<size_t>(1024, std::max<size_t>(1, nv / 16384));
   return nv * 48 + (nv + 63) / 64 * 8 + gp * ((size_t)QCAP * 4 + (size_t)CAND * 8 + 8) +
-         (size_t)(65536 + 2) * (4 * 4) + sizeof(Ctrl) + 2 * sizeof(RoundState) + 3 * 16 * 8 + 2 * (size_t)RT * 8 +
+         (size_t)(65536 + 2) * (4 * 4) + 3 * sizeof(Ctrl) + 2 * sizeof(RoundState) + 3 * 16 * 8 + 2 * (size_t)RT * 8 +
          sizeof(TeamSync) + sizeof(BlockOut);
 }
 
@@ -667,7 +667,8 @@ static ldd_status decompose_run(Workspace& w, const ldd_csr* g, const int64_t* s
 // road-like graphs: many rounds with small frontiers) go to one workgroup when they are small
 // (one workgroup reads them faster than round steps over the whole GPU synchronise; but its preparation and output take 1.8 ns a vertex, against 55 us for a
 // team's on 262,144 vertices, so few arcs on many vertices, the late levels of a block decomposition, take
-// 0.12 ms on a team and 0.7 ms alone), else to a team, which refuses a graph with a vertex of more than
+// 0.12 ms on a team and 0.7 ms alone; just above 2^14 vertices and below 2^15 arcs, Erdos-Renyi at beta 0.02 and 0.2 and a
+// path, 585, 212 and 788 us on a team, 909, 253 and 897 alone), else to a team, which refuses a graph with a vertex of more than
 // AUTO_TEAM_DEG_CAP arcs (one member would expand it alone), and that graph goes to the multi-block engines
 // too.
 // Measured (ms, launch engine -> team): rgg (6 arcs per vertex) 50K/200K/1M/4M vertices
@@ -704,7 +705,7 @@ static int tail_den_of(const ldd_options& o) {
 
 // One graph on the workgroup engine: one workgroup (WORKGROUP), or a team of K workgroups
 // (TEAM: blocks of them, by default by the size of the graph up to one per CU, at most the workgroups that can be resident at once, at
-// least 64 vertices per member) meeting at a device-memory barrier once per round.
+// least 64 vertices per member) meeting at a device-memory barrier once per step of one or more rounds.
 static ldd_status decompose_block(Workspace& w, const ldd_csr* g, const int64_t* shift_fix, int32_t* centre,
                                   int64_t* cut_edges, const ldd_options& opt, ldd_stats* stats, hipStream_t st,
                                   bool team, int deg_cap) {
@@ -949,8 +950,8 @@ ldd_status ldd_batch_workgroup(int32_t G, const int64_t* vtx_off, const int64_t*
     std::lock_guard<std::mutex> lk(w.mu);
     ldd_status s = ws_setup(w);
     if (s != LDD_OK) return s;
-    // one workgroup per CU by default: on the 512-graph benchmark batch one per CU ran 17% faster
-    // than two (6.35 vs 7.69 ms), the memory system being the shared resource
+    // One workgroup per CU by default, which is what its registers and LDS let be resident: more of them take
+    // their jobs when the first ones end.
     int grid = o.blocks > 0 ? o.blocks : w.num_cu;
     // Teams: a graph with more arcs than a workgroup's share of the batch (three quarters of all arcs over
     // the grid, at least 2^14; or team_arcs when given) runs on K = ceil(arcs / share) workgroups (at most

@@ -2011,7 +2011,7 @@ __device__ __forceinline__ void team_share(unsigned nf, unsigned K, unsigned m, 
 }
 
 // The rounds of a team: the same rounds and tail as block_rounds, in steps of one or more rounds
-// (team_step) with one barrier each.
+// (team_step1, team_steps) with one barrier each.
 __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
   const BlockJob j = job_of(sh);
   const int n = j.n;
