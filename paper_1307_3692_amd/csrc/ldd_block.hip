@@ -1115,7 +1115,7 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
         j.centre[v] = c[k];
         *pieces += c[k] == v;
       }
-      if (a1[k] - a[k] > HUGE_ROW) {
+      if (__builtin_expect(a1[k] - a[k] > HUGE_ROW, 0)) {
         const unsigned h = atomicAdd(&sh.nh3[0], 1u);
         if (h < HCAP) {
           sh.heavy[h] = HeavyRow{(u64)(unsigned)v << 32 | (unsigned)c[k], a[k], a1[k] - a[k]};
@@ -1157,9 +1157,11 @@ __device__ __forceinline__ void output_slice(const BlockJob& j, BlockShared& sh,
     if (bad) atomicOr(&sh.err, ERR_BAD_COL);
   }
   __syncthreads();
-  walk_heavy(j, sh, 0, CutRow{j, mask, *cut2});
-  __syncthreads();
-  if (threadIdx.x == 0) sh.err |= sh.er3[0];
+  if (__builtin_expect(sh.nh3[0] != 0, 0)) {
+    walk_heavy(j, sh, 0, CutRow{j, mask, *cut2});
+    __syncthreads();
+    if (threadIdx.x == 0) sh.err |= sh.er3[0];
+  }
 }
 
 // The same with the centres (at most 16 bits) kept in LDS.  Centres of the vertices [lo, hi) (INF: an isolated vertex, its own
@@ -1996,8 +1998,10 @@ __device__ __forceinline__ unsigned step_slack(const BlockJob& j) {
   return (unsigned)((float)STEP_SLACK * x * x);
 }
 
-__device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K, unsigned slack) {
-  if (spill || nf > STEP_SHARE * (unsigned)K) return 1;
+// most_rows: frontiers of as many take one round per step (0: all do).
+__device__ __forceinline__ int next_rounds(int rounds, unsigned before, unsigned nf, bool spill, int K, unsigned most_rows,
+                                           unsigned slack) {
+  if (spill || nf >= most_rows) return 1;
   const int most = nf > STEP_SMALL * (unsigned)K ? STEP_MAX : STEP_MAX_SMALL;
   if (nf <= before + before / 2 + slack) return 2 * rounds < most ? 2 * rounds : most;
   return rounds > 1 ? rounds / 2 : 1;
@@ -2034,7 +2038,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
   int r = team_next_nonempty(sh, 0, D);
   int step = 1;        // rounds of the next step
   const unsigned slack = step_slack(j);
-  const bool single = sh.maxdeg > (unsigned)STEP_ROW;
+  const unsigned most_rows = sh.maxdeg > (unsigned)STEP_ROW ? 0 : STEP_SHARE * (unsigned)K;
   bool clean = true;   // no entry of the queue was left over by a spill
   bool tail = false;
   // at most D / 1 steps wake, and every step moves every queued label one round on
@@ -2057,7 +2061,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       clean = true;
       r = team_next_nonempty(sh, r, D);
     }
-    step = single ? 1 : next_rounds(step, before, nf, sh.tspill, K, slack);
+    step = next_rounds(step, before, nf, sh.tspill, K, most_rows, slack);
     if (tail_next(j, n_active, settled, nf, D - r, clean)) {
       tail = true;
       break;
@@ -2119,7 +2123,7 @@ __device__ __attribute__((noinline)) void team_rounds(BlockShared& sh) {
       if (step > 1) nf = team_steps<true>(sh, cur, nxt, e0, e1, 0, 0, step, examined);
       else nf = team_step1<true>(sh, cur, nxt, e0, e1, 0, 0, false, -(k + 1), examined);
       sweeps += step;
-      step = single ? 1 : next_rounds(step, before, nf, sh.tspill, K, slack);
+      step = next_rounds(step, before, nf, sh.tspill, K, most_rows, slack);
     }
     settled = n_active;
   }
