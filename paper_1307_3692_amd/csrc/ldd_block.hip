@@ -664,6 +664,9 @@ __device__ __forceinline__ bool tail_next(const BlockJob& j, u64 n_active, u64 s
   return j.tail_den > 0 && left > 0 && left * (u64)j.tail_den <= n_active && left_rounds > TAIL_MIN_LEFT &&
          ((u64)nf * TAIL_IDLE <= left || (flood && nf >= left * TAIL_FLOOD));
 }
+// The tail's seed walks a row on one thread (0.7 us an arc), and the other members of a team wait for it no longer
+// than their barrier allows: a team with a row of more arcs runs its rounds to the end.
+constexpr int TAIL_ROW = 1 << 18;
 // A workgroup alone pays the tail's scan of every vertex against rounds of about 2.5 us each.
 constexpr int TAIL_SCAN = 4096;
 
@@ -1719,6 +1722,7 @@ __device__ __attribute__((noinline)) void team_prepare(BlockShared& sh) {
   if (tid == 0) {
     sh.err |= e;
     sh.maxdeg = (unsigned)maxdeg;
+    if (maxdeg > (u64)TAIL_ROW) sh.j.tail_den = 0;
     sh.delta = delta;
     sh.n_active = n_active;
   }

@@ -56,3 +56,16 @@ def test_star(ldd, n):
                                        torch.cat((ci, torch.from_numpy(gci).cuda())), torch.cat((s, gs)), team_arcs=1024)
     assert torch.equal(centre[:n], want) and torch.equal(centre[n:], alone)
     assert cuts == [leaves_cut, alone_cut]
+
+
+def test_star_whose_hub_is_left_to_the_tail(ldd):
+    """With tail_vertices = 1 the label-correcting tail may start after the first round, with the hub unreached: its
+    seed is one thread's."""
+    import torch
+    n, hub = 6_000_000, 2_000_000
+    rp, ci = star(n, hub)
+    s = torch.zeros(n, dtype=torch.int64, device="cuda")
+    s[5] = 40 * S  # a leaf: the hub is one round from it, the other leaves two
+    print(f"star {n}", flush=True)
+    centre, cut = ldd.decompose(rp, ci, s, 0.1, engine=4, blocks=16, tail_vertices=1)
+    assert bool((centre == 5).all()) and cut == 0
